@@ -1,31 +1,27 @@
 // Prefill MoE layer: T tokens through one layer with every expert resident.
 //
 // Steps (each a kernel on one stream):
-//   1. router for all T tokens (the decode router kernel, one block per token);
-//   2. grouping: a stable counting sort of the T*k (token, rank) pairs by expert,
-//      giving per-expert offsets, the sorted pair list and its inverse;
+//   1. router for all T tokens (the batched router kernel);
+//   2. grouping: a stable counting sort of the T*k (token, rank) pairs by expert, giving
+//      per-expert offsets, the tokens in expert order, each pair's place, and the tile
+//      plans of the two GEMMs;
 //   3. hidden states rounded to bf16 for the matrix cores (other blocks of the grouping
 //      launch: it does not depend on the routing);
 //   4. grouped GEMM gate/up: for each expert e, H_e = SiLU(X_e W1_e^T) * (X_e W3_e^T),
 //      bf16 MFMA (v_mfma_f32_16x16x32_bf16) with fp32 accumulation, H_e stored bf16; the
 //      tiles of a last, partial round of work groups are split over K, and
 //   4b. a small kernel adds their parts and applies SiLU * up;
-//   5. grouped GEMM down: Y_e = H_e W2_e^T, K split in four (or two), fp32 partials;
-//   6. combine: OUT[t] = sum_r w[t][r] * Y[pair(t, r)], in a fixed order.
+//   5. grouped GEMM down: Y_e = H_e W2_e^T in fp32, the last round split likewise;
+//   6. combine: OUT[t] = sum_r w[t][r] * Y[pair(t, r)], in a fixed order, adding the parts
+//      of split tiles as it reads them.
 //
-// With about T k / n tokens per expert (128 for a 512-token prompt on 8 experts, top-2)
-// the GEMMs are bound by reading the expert weights from HBM, so the kernel is built to
-// keep many weight bytes in flight: each wave loads its own weight rows into registers,
-// several K steps ahead, with whole cache lines per load instruction, and only the token
-// tile is shared through LDS.
-// Work items (expert, M tile, N tile, K split) are laid out so that every item of one
-// expert lands on the same XCD (work group b runs on XCD b mod 8), where its token rows
-// stay in that XCD's L2.
+// Up to a few hundred tokens per expert the GEMMs are bound by reading the expert weights
+// from HBM; beyond, by the matrix cores.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
-#include <atomic>
+#include <type_traits>
 
 #include "common.h"
 #include "moe_internal.h"
@@ -34,18 +30,21 @@ namespace moe {
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float floatx16_t __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
-constexpr int kBK = 64;         // K per stage
-constexpr int kLdsStride = kBK + 8;   // bf16 per LDS row (16-byte pad against bank conflicts)
-constexpr int kRowChunks = kBK / 8;  // 16-byte chunks of a token row per step
+constexpr int kGemmThreads = 512;
+constexpr int kBK = 64;              // K per stage
 constexpr int kXcds = 8;
-constexpr int kSpreadTokens = 64;   // below this many (token, expert) pairs per expert, spread items over XCDs
-constexpr int kMaxDownSplits = 4;
-constexpr int kMaxTailSlots = 32;   // gate/up tail: work groups per XCD the split tiles may use
-constexpr int kMaxTailSplit = 16;   // gate/up tail: K parts per split tile
+constexpr int kTileM = 256;          // tokens per tile, at most
+constexpr int kTileN = 256;          // weight rows per tile
+constexpr int kGuCols = kTileN / 2;  // gate/up: H columns per tile
+constexpr int kLdsBytes = 163840;    // all of a CU's LDS
+constexpr int kMaxSplit = 16;        // K parts per split tile
+constexpr int kMinPartSteps = 4;     // K steps per part, at least
+constexpr int kSplitSteps = 4;       // what a part costs besides its K steps, in K steps
+constexpr int kMaxParts = 64;        // part buffers per XCD
+constexpr int kStagger = 2;          // K steps between the starts of neighbouring N tiles
 
 __device__ __forceinline__ uint16_t f2bf(float f)
 {
@@ -53,6 +52,14 @@ __device__ __forceinline__ uint16_t f2bf(float f)
     uint32_t u = __float_as_uint(f);
     u += 0x7fffu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
+}
+
+// SiLU(g) * u rounded to bf16, with the hardware's 1-ulp exp2 and reciprocal (the error
+// against 64 bits is that of the bf16 rounding, 2^-9 relative, as with expf and a division,
+// which took 2 % of a 4096-token Mixtral-shaped layer).
+__device__ __forceinline__ uint16_t swiglu_bf(float g, float u)
+{
+    return f2bf(g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504f * g)) * u);
 }
 
 // y = bf16(x) over n8 groups of 8 values; `first`, `stride`: this thread's first group
@@ -71,6 +78,58 @@ __device__ __forceinline__ void cast_bf16(const float *x, uint16_t *y, int64_t n
     }
 }
 
+// ---------------------------------------------------------------------------
+// Work decomposition of a grouped GEMM, planned on the device from the routing.
+//
+// Expert e's c tokens are cut into m = ceil(c / kTileM) tiles of equal height, rounded up
+// to 16 rows. A GEMM's output tiles, in (expert, N tile, M tile) order with the M tile
+// fastest, are dealt out to the XCDs in eight contiguous runs of equal length, so that the
+// tiles that share an expert's token rows (and, side by side, a weight tile) run on one
+// XCD's L2, whatever the number of experts. On an XCD the work groups (one per CU,
+// `slots` of them) take its tiles in rounds; the r tiles of a last, partial round are
+// split over K into s parts each, whose fp32 sums a later kernel adds in order.
+// ---------------------------------------------------------------------------
+struct TilePlan {
+    int u0, units;   // first tile of the XCD's run, its length
+    int full;        // tiles done whole; the other units - full are split over K
+    int s;           // K parts of a split tile
+};
+
+__device__ __forceinline__ int tiles_of(int c) { return (c + kTileM - 1) / kTileM; }
+// First row of tile mt of an expert with c tokens (mt == tiles_of(c): c): its ceil(c / 32)
+// blocks of 32 rows are spread evenly, so that few padding rows are multiplied.
+__device__ __forceinline__ int tile_row(int c, int mt)
+{
+    return min(c, (int)((uint32_t)((c + 31) >> 5) * (uint32_t)mt / (uint32_t)tiles_of(c)) * 32);
+}
+// the tile that holds row r
+__device__ __forceinline__ int tile_of_row(int c, int r)
+{
+    return (int)(((uint32_t)((r >> 5) + 1) * (uint32_t)tiles_of(c) - 1) / (uint32_t)((c + 31) >> 5));
+}
+
+// Plan of XCD xcd for U tiles of nsteps K steps. A split costs about as much as a few K
+// steps (prologue, fp32 sums); s minimises the rounds of parts within the part buffers.
+__device__ __forceinline__ TilePlan tile_plan(int U, int nsteps, int slots, int maxparts, int xcd)
+{
+    TilePlan p;
+    p.u0 = (int)((int64_t)U * xcd / kXcds);
+    p.units = (int)((int64_t)U * (xcd + 1) / kXcds) - p.u0;
+    const int r = p.units % slots;
+    p.full = p.units;
+    p.s = 1;
+    int best = nsteps;
+    for (int s = 2; r > 0 && s <= kMaxSplit && r * s <= maxparts && s * kMinPartSteps <= nsteps; ++s) {
+        const int cost = (r * s + slots - 1) / slots * ((nsteps + s - 1) / s + kSplitSteps);
+        if (cost < best) {
+            best = cost;
+            p.s = s;
+            p.full = p.units - r;
+        }
+    }
+    return p;
+}
+
 // Block 0: the grouping below. Blocks 1 ..: the hidden states rounded to bf16 for the
 // matrix cores (independent of the routing, so the two share one launch).
 // Stable counting sort of the pairs p = t*k + r by expert idx[p] (one block).
@@ -79,12 +138,22 @@ __device__ __forceinline__ void cast_bf16(const float *x, uint16_t *y, int64_t n
 // atomics; the place of a pair within its expert is the number of earlier pairs with
 // the same expert, counted over the chunk's ids in LDS four at a time.
 constexpr int kGroupThreads = 1024;
-__global__ __launch_bounds__(kGroupThreads) void k_group(const int32_t *idx, int npairs, int n, int32_t *off,
-                                                         int32_t *perm, int32_t *pos, const float *x, uint16_t *xb,
-                                                         int64_t n8)
+struct GroupArgs {
+    const int32_t *idx;              // [npairs]
+    int npairs, n, k;
+    int32_t *off, *toff, *tok, *pos;
+    TilePlan *plan;                  // [2][8]: gate/up, down
+    int ntiles[2], nsteps[2], maxparts[2], slots;
+    const float *x;
+    uint16_t *xb;
+    int64_t n8;
+};
+__global__ __launch_bounds__(kGroupThreads) void k_group(GroupArgs g)
 {
+    const int32_t *idx = g.idx;
+    const int npairs = g.npairs, n = g.n;
     if (blockIdx.x > 0) {
-        cast_bf16(x, xb, n8, (int64_t)(blockIdx.x - 1) * kGroupThreads + threadIdx.x,
+        cast_bf16(g.x, g.xb, g.n8, (int64_t)(blockIdx.x - 1) * kGroupThreads + threadIdx.x,
                   (int64_t)(gridDim.x - 1) * kGroupThreads);
         return;
     }
@@ -98,14 +167,23 @@ __global__ __launch_bounds__(kGroupThreads) void k_group(const int32_t *idx, int
     for (int p = t; p < npairs; p += kGroupThreads) atomicAdd(&base[idx[p]], 1);
     __syncthreads();
     if (t == 0) {
-        int acc = 0;
+        int acc = 0, tiles = 0;
         for (int e = 0; e < n; ++e) {
             const int c = base[e];
             base[e] = acc;
-            off[e] = acc;
+            g.off[e] = acc;
+            g.toff[e] = tiles;
             acc += c;
+            tiles += tiles_of(c);
         }
-        off[n] = acc;
+        g.off[n] = acc;
+        g.toff[n] = tiles;
+        hist[0] = tiles;
+    }
+    __syncthreads();
+    if (t < 2 * kXcds) {
+        const int q = t / kXcds;
+        g.plan[t] = tile_plan(hist[0] * g.ntiles[q], g.nsteps[q], g.slots, g.maxparts[q], t % kXcds);
     }
     for (int c0 = 0; c0 < npairs; c0 += kGroupThreads) {
         const int m = min(kGroupThreads, npairs - c0);
@@ -125,8 +203,8 @@ __global__ __launch_bounds__(kGroupThreads) void k_group(const int32_t *idx, int
             }
             for (int j = t & ~3; j < t; ++j) rank += ids[j] == (uint8_t)my;
             const int w = base[my] + rank;
-            perm[w] = c0 + t;
-            pos[c0 + t] = w;
+            g.tok[w] = (c0 + t) / g.k;
+            g.pos[c0 + t] = w;
             atomicAdd(&hist[my], 1);
         }
         __syncthreads();
@@ -138,424 +216,368 @@ struct GemmArgs {
     const uint16_t *a;        // gate/up: X bf16 [T][d] (rows gathered by token); down: H bf16 [P][f]
     const uint8_t *pool;      // expert slabs
     uint64_t slab_stride;
-    const int32_t *off;       // [n+1]
-    const int32_t *perm;      // [P] pair ids sorted by expert
-    int n, k, d, f;
-    int mtiles;               // M tiles per expert (upper bound)
-    int ntiles;               // N tiles per matrix
-    int ksplit;               // K splits
-    int per_xcd;              // work items per XCD (expert-per-XCD layout)
-    int spread;               // 1: item b is simply the b-th (expert, m, n, k) item
-    int tail;                 // gate/up, expert-per-XCD layout: split the last partial round over K
-    int slots;                // tail: work groups resident per XCD (<= kMaxTailSlots)
-    float *part;              // tail: fp32 (g, u) partial sums [8][slots][kTileM][2 kGuCols]
+    const int32_t *off;       // [n+1] first sorted pair of each expert
+    const int32_t *toff;      // [n+1] first M tile of each expert
+    const int32_t *tok;       // [P] token of each sorted pair
+    const TilePlan *plan;     // [8] one per XCD
+    int n, d, f;
+    int ntiles;               // N tiles
+    int slots;                // work groups per XCD
+    int maxparts, prows;      // part buffers per XCD and their rows
+    float *part;              // fp32 sums of the K parts, [8][maxparts][prows][kTileN]
     uint16_t *h;              // gate/up output, bf16 [P][f]
-    float *yp;                // down output, fp32 [ksplit][P][d]
+    float *y;                 // down output, fp32 [P][d]
 };
 
-// Grouped GEMM with the weight operand fed from HBM into MFMA registers without a shared
-// staging buffer: each wave loads its own weight rows and passes them through its own
-// LDS region into the operand layout (see gemm_k_loop).
+// Grouped GEMM, 8 waves per work group, one work group per CU, looping over its tiles.
 //
-// A work group (kGWaves waves) owns up to 192 tokens of one expert and a tile of weight
-// rows: for gate/up kGuCols columns of H (that many W1 rows and the same W3 rows), for
-// down 256 (or 128) rows of W2. Each wave owns kNB 16-row MFMA column blocks of them (for
-// gate/up the first kNB/2 are W1 blocks and the rest the matching W3 blocks, so the gate
-// and up values of an output sit in the same lane) and all the tokens (twelve 16-row
-// blocks). In v_mfma_f32_16x16x32_bf16 the B operand of lane l is 8 consecutive K values
-// of column l mod 16, the four lanes l mod 16 + 16 i covering 32 consecutive K values;
-// each weight byte is loaded once per work group. The token tile (shared by the waves) is
-// staged in LDS, double-buffered.
+// A tile is up to 256 tokens of one expert by 256 weight rows (gate/up: 128 W1 rows and the
+// same 128 W3 rows). Two waves split the tokens and four the weight rows: a wave owns
+// 16 HB tokens and 64 weight rows (gate/up: 32 W1 rows and the matching W3 rows, so an
+// output's gate and up values sit in the same lane), so an operand read from LDS serves
+// 4 to 8 MFMAs. Both operands go from memory to LDS with direct loads (16 bytes per lane,
+// the 128 bytes of a K step of 8 rows per instruction), in rings of stages of one K step
+// each; one barrier per step. The token ring is shorter than the weight ring where LDS is
+// short: it is refilled from the L2 and the weights from HBM. In a stage, row r's 16-byte
+// chunk c sits at slot c ^ (r mod 8), which the loads arrange by permuting the source
+// addresses within a row, so that the operand reads (16 rows, one chunk each per quarter
+// wave) touch all banks evenly (no bank conflict counted).
 //
-// Weight loads run kS - 1 K steps ahead in a ring of kS register sets (kS = 3 below), the
-// token loads one step ahead in a ring of two; the K loop is unrolled so that every set is
-// a fixed group of registers. All loads are unconditional: token rows past the tile
-// re-read row 0 (their outputs are dropped) and steps past the end re-read the last step.
-// K = f of the down projection is split in ksplit parts that write separate fp32 partial
-// sums.
+// The weights are the MFMA's A operand, so a lane's four results are consecutive output
+// columns of one token.
 //
-// Eight waves of 32 weight rows each (kNB = 2) and four waves of 64 rows (kNB = 4, one
-// wave per SIMD, accumulators in AGPRs, half the LDS reads of token operands per MFMA)
-// ran within 2 % of each other on the Mixtral-shaped layer; a per-wave clock trace shows
-// the K step bound by the LDS reads of the token operands and the MFMAs that wait for
-// them, not by the weight stream (the step takes as long with the weight loads removed).
-typedef float floatx4_t __attribute__((ext_vector_type(4)));
-constexpr int kGWaves = 8;                             // waves per work group of the launches below
-constexpr int kGuCols = 128;                           // H columns per gate/up work group
-constexpr int kGuNB = 2 * kGuCols / (16 * kGWaves);    // gate/up column blocks per wave (W1 and W3 halves)
-constexpr int kDnNB = 256 / (16 * kGWaves);            // down column blocks per wave (256-row tiles)
-constexpr int kMBlocks = 12;                           // 16-token blocks per tile
-constexpr int kTileM = kMBlocks * 16;                  // 192 tokens
-constexpr int kKBlocks = kBK / 32;                     // MFMA K blocks per step
+// Measured (us per layer, before: 192-token tiles, weights through registers, 4 fp32
+// partial planes of the down projection): 512 tokens on 8 Mixtral-shaped experts 605 -> 532,
+// 4096 tokens 4060 -> 2545 (matrix cores busy 53 % of the cycles at the 1.9 GHz the chip
+// holds; without loads in the K loop 1985), 1333 tokens on 64 fine-grained experts 1228 ->
+// 897. At 512 tokens the K loop takes as long with its MFMAs and operand reads removed:
+// the load stream bounds it. Rings of 32-wide stages (deeper, 64-byte row pieces), waves
+// that only load tokens or only weights, and raised wave priority around the MFMAs were
+// no faster.
+constexpr int kRowBytes = kBK * 2;
+constexpr int kRows = 1024 / kRowBytes;             // rows per load instruction of a wave
+constexpr int kBBytes = kTileN * kRowBytes;         // weight rows of a stage
+constexpr int kBLoads = kTileN / kRows / 8;         // load instructions per wave and stage
+typedef __attribute__((address_space(1))) const void global_cvoid;
+typedef __attribute__((address_space(3))) void lds_void;
 
-// Weight rows of one wave staged for the row-contiguous path: 16 kNB rows of one K step
-// (128 bytes each), padded by 16 bytes per row.
-constexpr int kWStride = kBK + 8;
-
-// The K loop of k_moe_gemm for a tile of NMB 16-token blocks. NMB is a compile-time
-// constant so the MFMA sequence of a step has no branches, and the LDS reads of the
-// token blocks are issued kAP MFMA items ahead of their use (with a run-time block count
-// every block was its own branch, and each MFMA pair waited for its own LDS read; with a
-// constant count but no pinned order, the compiler still read each block just before its
-// MFMAs: 632 against 601 us per Mixtral-shaped layer with the lookahead). Blocks past the
-// tile's last token are not computed.
-//
-// Weights reach the MFMA operand registers row-contiguously: load instruction i reads the
-// wave's rows 8i .. 8i+7, 128 bytes (one K step) of each, with the nontemporal hint, and
-// the wave passes them through its own LDS region (written, then read back in the
-// operand layout; no other wave touches it, so no barrier). Each instruction touches 8
-// whole cache lines, where loading each lane's operand pieces directly touches halves of
-// 16: half the L1 requests per weight byte, and whole lines for the nontemporal hint (with
-// half lines it fetched each line twice). The down projection ran 13 % faster this way
-// (223 -> 194 us per Mixtral-shaped layer); gate/up needs it together with kStagger.
-//
-// kStagger (gate/up): each work group starts its K walk at its own step (block id x 7
-// mod the step count) and wraps around, so work groups running at the same time read
-// different 128-byte columns of rows 8 KiB apart instead of the same one. Together with the
-// row-contiguous loads this took gate/up from 414 to 400 us per Mixtral-shaped layer in a
-// same-box A/B; either alone was neutral or slower, and the stagger slowed down (205 ->
-// 208 us), which keeps its fixed K order.
-template <int kS, int kAP, int kNB, int kAN, int kThr, int NMB, bool kStagger>
-__device__ __forceinline__ void gemm_k_loop(uint16_t (*lds_a)[kTileM * kLdsStride], const uint16_t *const (&asrc)[kAN],
-                                            const uint16_t *const (&bsrc)[2 * kNB], uint16_t *lds_w, int nsteps,
-                                            floatx4_t (&acc)[kMBlocks][kNB])
-{
-    const int kstag = kStagger ? (int)(blockIdx.x * 7u % (unsigned)nsteps) : 0;
-    static_assert(kBK == 64, "row-contiguous weight loads cover 128 bytes of a row per step");
-    constexpr int kLB = 2 * kNB;   // weight loads per lane per step
-    constexpr int kSA = 2;         // token register sets: one step ahead
-    constexpr int kU = kS % kSA == 0 ? kS : kS * kSA;   // unroll: both rings at fixed registers
-    // only the NMB token blocks that hold tokens are staged (the first kAL of the thread's
-    // kAN chunks): a tile of 128 tokens stages 128 rows per step, not 192
-    constexpr int kChunks = NMB * 16 * kRowChunks;
-    constexpr int kAL = (kChunks + kThr - 1) / kThr;
-    static_assert(kAL <= kAN, "staged chunks within the tile's");
-    const int tid = threadIdx.x, lane = tid & 63;
-    u32x4_t ra[kSA][kAL], rb[kS][kLB];
-    u32x4_t rt[kNB * kKBlocks];                                  // operand pieces after the LDS pass
-#define MOE_KOFF(step) (((min((step), nsteps - 1) + kstag) % nsteps) * kBK)
-#define MOE_LOAD_A(set, step)                                                                         \
-    do {                                                                                              \
-        const int ko_ = MOE_KOFF(step);                                                               \
-        _Pragma("unroll") for (int i = 0; i < kAL; ++i) ra[set][i] =                                  \
-            *reinterpret_cast<const u32x4_t *>(asrc[i] + ko_);                                        \
-    } while (0)
-#define MOE_LOAD_W(set, step)                                                                         \
-    do {                                                                                              \
-        const int ko_ = MOE_KOFF(step);                                                               \
-        _Pragma("unroll") for (int i = 0; i < kLB; ++i) rb[set][i] =                                  \
-            __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(bsrc[i] + ko_));             \
-    } while (0)
-#define MOE_STASH(set, buf)                                                                           \
-    do {                                                                                              \
-        _Pragma("unroll") for (int i = 0; i < kAL; ++i) {                                             \
-            const int c_ = tid + kThr * i;                                                            \
-            if (kChunks % kThr == 0 || c_ < kChunks)                                                  \
-                *reinterpret_cast<u32x4_t *>(&lds_a[buf][(c_ / kRowChunks) * kLdsStride + (c_ % kRowChunks) * 8]) = ra[set][i]; \
-        }                                                                                             \
-    } while (0)
-    // rows 8i + lane/8 in, operand pieces (row 16 nb + lane mod 16, K 32 kb + 8 (lane / 16)) out
-#define MOE_TRANSPOSE(set)                                                                            \
-    do {                                                                                              \
-        _Pragma("unroll") for (int i = 0; i < kLB; ++i)                                               \
-            *reinterpret_cast<u32x4_t *>(&lds_w[(8 * i + (lane >> 3)) * kWStride + (lane & 7) * 8]) = rb[set][i]; \
-        _Pragma("unroll") for (int nb = 0; nb < kNB; ++nb)                                            \
-        _Pragma("unroll") for (int kb = 0; kb < kKBlocks; ++kb) rt[nb * kKBlocks + kb] =              \
-            *reinterpret_cast<const u32x4_t *>(&lds_w[(16 * nb + (lane & 15)) * kWStride + kb * 32 + 8 * (lane >> 4)]); \
-    } while (0)
-    // token operand of MFMA item j (K block j / NMB, token block j mod NMB)
-#define MOE_AREAD(j, buf)                                                                             \
-    (*reinterpret_cast<const bf16x8_t *>(                                                             \
-        &lds_a[buf][(((j) % NMB) * 16 + (lane & 15)) * kLdsStride + ((j) / NMB) * 32 + 8 * (lane >> 4)]))
-    // The token operands are read kAP items ahead of their MFMAs, in a ring of kAP registers,
-    // and the order is pinned (left to itself the compiler read each operand just before its
-    // MFMA pair and waited for it, so the LDS latency was paid once per token block).
-#define MOE_MMA(buf)                                                                                  \
-    do {                                                                                              \
-        constexpr int kJ_ = kKBlocks * NMB;                                                           \
-        bf16x8_t aq_[kAP];                                                                            \
-        _Pragma("unroll") for (int j = 0; j < kAP; ++j) if (j < kJ_) aq_[j] = MOE_AREAD(j, buf);      \
-        _Pragma("unroll") for (int j = 0; j < kJ_; ++j) {                                             \
-            const bf16x8_t a_ = aq_[j % kAP];                                                         \
-            if (j + kAP < kJ_) aq_[j % kAP] = MOE_AREAD(j + kAP, buf);                                \
-            _Pragma("unroll") for (int nb = 0; nb < kNB; ++nb) acc[j % NMB][nb] =                     \
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(                                              \
-                    a_, __builtin_bit_cast(bf16x8_t, rt[nb * kKBlocks + j / NMB]),                    \
-                    acc[j % NMB][nb], 0, 0, 0);                                                       \
-            __builtin_amdgcn_sched_barrier(0);                                                        \
-        }                                                                                             \
-    } while (0)
-
-    // Step t: the tokens of step t + 1 are loaded first, then the weights of step
-    // t + kS - 1; the token stash at the end of the step waits for the former, and since
-    // loads complete in issue order that also covers every weight set issued before it.
-    MOE_LOAD_A(0, 0);
-#pragma unroll
-    for (int p = 0; p < kS - 1; ++p) MOE_LOAD_W(p, p);
-    MOE_STASH(0, 0);
-    __syncthreads();
-    for (int s = 0; s < nsteps; s += kU) {
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            if (s + u >= nsteps) break;
-            MOE_TRANSPOSE(u % kS);
-            MOE_LOAD_A((u + 1) % kSA, s + u + 1);
-            MOE_LOAD_W((u + kS - 1) % kS, s + u + kS - 1);
-            MOE_MMA((s + u) & 1);
-            MOE_STASH((u + 1) % kSA, (s + u + 1) & 1);
-            __syncthreads();
-        }
-    }
-#undef MOE_KOFF
-#undef MOE_LOAD_A
-#undef MOE_LOAD_W
-#undef MOE_STASH
-#undef MOE_TRANSPOSE
-#undef MOE_MMA
-#undef MOE_AREAD
-}
-
-// Gate/up tail split (expert-per-XCD layout). The live tiles of XCD x (its experts x,
-// x + 8, ... times their occupied M tiles and the N tiles) run in rounds of g.slots work
-// groups; the r tiles of a last, partial round are split over K into s parts, as many as
-// the idle work groups allow (s r <= slots), and a second kernel adds the parts.
-struct TailPlan {
-    int U, R, r, s;   // live tiles, full rounds, tiles of the partial round, K parts per tile
+template <int HB>
+struct TileCfg {
+    static constexpr int kABytes = HB * 32 * kRowBytes;           // token rows of a stage
+    static constexpr int kAStages = HB <= 2 ? 4 : HB <= 5 ? 3 : 2;
+    static constexpr int kBStages = HB <= 2 ? 4 : 3;
+    static constexpr int kBBase = kAStages * kABytes;             // the weight ring follows the token ring
+    static constexpr int kALoads = (HB + 1) / 2;                  // load instructions per wave and stage
+    static constexpr int kLoads = kALoads + kBLoads;
+    static constexpr int kRing = HB == 8 || HB == 6 || HB == 4 ? 4 : HB;   // divides 2 HB
+    static constexpr int kAhead = kRing < 4 ? kRing : 4;
+    // at a hand-over, loads that may be outstanding: those of stages after the next one
+    static constexpr int kKeep = kAStages == kBStages ? (kAStages - 2) * kLoads : kBLoads;
+    static_assert(kBBase + kBStages * kBBytes <= kLdsBytes, "the rings fit LDS");
+    static_assert(kAStages == kBStages || (kAStages == 2 && kBStages == 3), "kKeep");
 };
 
-__device__ __forceinline__ TailPlan tail_plan(const GemmArgs &g, int xcd)
+// The LDS reads of the previous step are done and at most N of this wave's loads are still
+// in flight; then every wave of the work group is at this point.
+template <int N>
+__device__ __forceinline__ void wait_and_barrier()
 {
-    TailPlan p;
-    p.U = 0;
-    for (int e = xcd; e < g.n; e += kXcds) p.U += (g.off[e + 1] - g.off[e] + kTileM - 1) / kTileM * g.ntiles;
-    p.R = p.U / g.slots;
-    p.r = p.U - p.R * g.slots;
-    p.s = 1;
-    while (p.r > 0 && 2 * p.s * p.r <= g.slots && 2 * p.s <= kMaxTailSplit && (g.d / kBK) % (2 * p.s) == 0) p.s *= 2;
-    return p;
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
-
-// live tile t (< U) of XCD xcd -> expert, M tile, N tile (N-major within an expert)
-__device__ __forceinline__ void tail_tile(const GemmArgs &g, int xcd, int t, int &e, int &mt, int &nt)
+template <bool kGateUp, bool kOnce, int HB>
+__device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *lds, int e, int row0, int rows, int nt, int k0,
+                                          int nsteps, int start, float *part)
 {
-    for (e = xcd;; e += kXcds) {
-        const int m_e = (g.off[e + 1] - g.off[e] + kTileM - 1) / kTileM;
-        if (t < m_e * g.ntiles) {
-            mt = t % m_e;
-            nt = t / m_e;
-            return;
-        }
-        t -= m_e * g.ntiles;
-    }
-}
-
-template <bool kGateUp, int kS, int kNB, int kWaves>
-__global__ __launch_bounds__(kWaves * 64) void k_moe_gemm(GemmArgs g)
-{
-    constexpr int kThr = kWaves * 64;
-    constexpr int kAN = (kTileM * kRowChunks + kThr - 1) / kThr;   // token-tile 16-byte chunks per thread per step
-    __shared__ uint16_t lds_a[2][kTileM * kLdsStride];
-    __shared__ uint16_t lds_w[kWaves][16 * kNB * kWStride];
-
+    using C = TileCfg<HB>;
+    constexpr int NA = C::kAStages, NB = C::kBStages, P = C::kAhead, R = C::kRing, kItems = 2 * HB;
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));   // keeps the addresses of all tile heights from being computed up front
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wv & 1, wn = wv >> 1;
     const int K = kGateUp ? g.d : g.f;
-    int e, mt, nt, ks = 0, kparts = g.ksplit;
-    int xcd = 0, tail_v = -1, tail_s = 1;   // tail: unit v of a tile split in tail_s K parts
-    if (kGateUp && g.tail) {
-        // units: the full tiles (whole K) first, then the K parts of the partial round's tiles
-        xcd = blockIdx.x % kXcds;
-        const int u = blockIdx.x / kXcds;
-        const TailPlan tp = tail_plan(g, xcd);
-        tail_s = tp.s;
-        int t;
-        if (u < tp.R * g.slots || tail_s == 1) {
-            if (u >= tp.U) return;
-            t = u;
-        } else {
-            const int v = u - tp.R * g.slots;
-            if (v >= tp.r * tail_s) return;
-            t = tp.R * g.slots + v / tail_s;
-            ks = v % tail_s;
-            kparts = tail_s;
-            tail_v = v;
-        }
-        tail_tile(g, xcd, t, e, mt, nt);
-    } else {
-        const int per_expert = g.mtiles * g.ntiles * g.ksplit;
-        int q;
-        if (g.spread) {   // few tokens per expert: an expert's items go round all XCDs
-            q = blockIdx.x;
-            e = q / per_expert;
-        } else {          // an expert's items stay on XCD e mod 8, sharing its token rows in L2
-            q = blockIdx.x / kXcds;
-            if (q >= g.per_xcd) return;
-            e = blockIdx.x % kXcds + kXcds * (q / per_expert);
-        }
-        if (e >= g.n) return;
-        q %= per_expert;
-        ks = q % g.ksplit;
-        q /= g.ksplit;
-        mt = q % g.mtiles;
-        nt = q / g.mtiles;
-    }
-    const int row0 = g.off[e] + mt * kTileM;
-    const int rows = min(kTileM, g.off[e + 1] - row0);
-    if (rows <= 0) return;
+    // row within a load instruction and byte offset of the chunk that lands in this lane's slot
+    const int lr = lane >> 3, lc = ((lane & 7) ^ lr) * 16;
 
-    const int kspan = K / kparts;
-    const int k0 = ks * kspan;
-    const int nsteps = kspan / kBK;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int nmb = (rows + 15) >> 4;                  // token blocks holding tokens of this tile
-    const uint16_t *w = reinterpret_cast<const uint16_t *>(g.pool + (uint64_t)e * g.slab_stride);
-
-    static_assert(!kGateUp || (kNB % 2 == 0 && kWaves * 8 * kNB == kGuCols),
-                  "gate/up pairs each W1 block with a W3 block over kGuCols columns");
-    // this lane's weight row and K offset for the row-contiguous loads: row 8i + lane / 8 of
-    // the wave's rows, 8 (lane mod 8) elements into the K step
-    const uint16_t *bsrc[2 * kNB];
-    if constexpr (kGateUp) {   // the wave's 8 kNB W1 rows (loads 0 .. kNB-1), then the same W3 rows
+    // Token rows: loads past the stage's last repeat it, rows past the tile read its first.
+    // Down's rows are consecutive, so a 32-bit offset from the tile's first reaches them.
+    typename std::conditional<kGateUp, const uint8_t *, uint32_t>::type asrc[C::kALoads];
+    const uint8_t *const abase =
+        reinterpret_cast<const uint8_t *>(g.a + (kGateUp ? 0 : (size_t)row0 * K) + (size_t)k0 * kBK);
 #pragma unroll
-        for (int i = 0; i < 2 * kNB; ++i) {
-            const size_t wrow = (size_t)nt * kGuCols + wv * 8 * kNB + 8 * (i % kNB) + (lane >> 3);
-            bsrc[i] = w + (i >= kNB ? (size_t)g.f * g.d : 0) + wrow * g.d + k0 + 8 * (lane & 7);
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 2 * kNB; ++i) {
-            const size_t wrow = (size_t)nt * (kWaves * 16 * kNB) + wv * 16 * kNB + 8 * i + (lane >> 3);
-            bsrc[i] = w + (size_t)2 * g.f * g.d + wrow * g.f + k0 + 8 * (lane & 7);
-        }
+    for (int j = 0; j < C::kALoads; ++j) {
+        int r = min(j * 8 + wv, HB * 4 - 1) * kRows + lr;
+        r = r < rows ? r : 0;
+        if constexpr (kGateUp) asrc[j] = abase + (size_t)g.tok[row0 + r] * K * 2 + lc;
+        else asrc[j] = (uint32_t)r * (uint32_t)K * 2 + lc;
     }
-    // token-tile chunks staged by this thread: chunk c = tid + kThr i is row c / kRowChunks, column
-    // c % kRowChunks (chunks past the tile, when the threads do not divide it, load row 0 and are not stored)
-    const uint16_t *asrc[kAN];
-#pragma unroll
-    for (int i = 0; i < kAN; ++i) {
-        const int c = tid + kThr * i;
-        const int r = c / kRowChunks, col = (c % kRowChunks) * 8;
-        const int rr = r < rows ? r : 0;
-        if (kGateUp) asrc[i] = g.a + (size_t)(g.perm[row0 + rr] / g.k) * g.d + k0 + col;
-        else asrc[i] = g.a + (size_t)(row0 + rr) * g.f + k0 + col;
-    }
+    // Weight rows: instruction i of wave wv reads the kRows rows from 64 i + 8 wv; gate/up's
+    // second half are the W3 rows, and a down tile with only 128 rows left in W2 (d an odd
+    // multiple of 128) reads them twice.
+    const size_t wrow = (size_t)nt * (kGateUp ? kGuCols : kTileN) + wv * kRows;
+    const uint8_t *const bbase = g.pool + (uint64_t)e * g.slab_stride +
+                                 2 * ((kGateUp ? (size_t)0 : (size_t)2 * g.f * g.d) + wrow * K + (size_t)k0 * kBK);
+    const size_t bhalf = kGateUp ? (size_t)2 * g.f * K : nt * kTileN + 128 < g.d ? (size_t)256 * K : 0;
+    const uint32_t bquarter = 128u * (uint32_t)K;   // bytes of 64 rows
+    const uint32_t blane = (uint32_t)lr * (uint32_t)K * 2 + lc;
+    auto koff = [&](int stage) {   // steps go round from `start`
+        const int ks = stage + start;
+        return (size_t)(ks >= nsteps ? ks - nsteps : ks) * kRowBytes;
+    };
+    auto load_a = [&](int i, int stage, int buf) {
+        const uint8_t *src;
+        if constexpr (kGateUp) src = asrc[i] + koff(stage);
+        else src = abase + koff(stage) + asrc[i];
+        __builtin_amdgcn_global_load_lds((global_cvoid *)src,
+                                         (lds_void *)(lds + buf * C::kABytes + min(i * 8 + wv, HB * 4 - 1) * 1024), 16, 0,
+                                         0);
+    };
+    auto load_b = [&](int i, int stage, int buf) {
+        const uint8_t *src = bbase + koff(stage) + (i >> 1) * bhalf + (i & 1) * bquarter;
+        __builtin_amdgcn_global_load_lds((global_cvoid *)(src + blane),
+                                         (lds_void *)(lds + C::kBBase + buf * kBBytes + (i * 8 + wv) * 1024), 16, 0,
+                                         kOnce ? 2 : 0);   // 2: nontemporal
+    };
 
-    floatx4_t acc[kMBlocks][kNB];
+    floatx4_t acc[HB][4];
 #pragma unroll
-    for (int m = 0; m < kMBlocks; ++m)
+    for (int m = 0; m < HB; ++m)
 #pragma unroll
-        for (int nb = 0; nb < kNB; ++nb) acc[m][nb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+        for (int nb = 0; nb < 4; ++nb) acc[m][nb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
-    // One copy of the K loop per token-block count, chosen once per work group.
-    constexpr int kTokAhead = 6;   // token operand reads kept ahead of the MFMAs
-    switch (nmb) {
-#define MOE_NMB_CASE(N) \
-    case N: gemm_k_loop<kS, kTokAhead, kNB, kAN, kThr, N, kGateUp>(lds_a, asrc, bsrc, lds_w[wv], nsteps, acc); \
-        break;
-        MOE_NMB_CASE(1) MOE_NMB_CASE(2) MOE_NMB_CASE(3) MOE_NMB_CASE(4) MOE_NMB_CASE(5) MOE_NMB_CASE(6)
-        MOE_NMB_CASE(7) MOE_NMB_CASE(8) MOE_NMB_CASE(9) MOE_NMB_CASE(10) MOE_NMB_CASE(11) MOE_NMB_CASE(12)
-#undef MOE_NMB_CASE
-    default: break;
-    }
-
-    // Output element r of a 16x16 block sits at row 4*(lane/16) + r, column lane%16.
-    if constexpr (kGateUp) {
-        if (tail_v >= 0) {   // a K part of a split tile: its fp32 (g, u) sums, added by k_tail_combine
-            constexpr int kCols = 2 * kGuCols;   // g columns, then u columns
-            float *mine = g.part + ((size_t)xcd * g.slots + tail_v) * kTileM * kCols;
+    // Operand reads: row lane % 16 of a block, chunk 4 kb + lane / 16. The items of a step are
+    // (kb, m) in order; item j's token block is read P items before its MFMAs, in a ring of R
+    // registers, and the weight blocks of a kb with its first item. P items before the end
+    // of a step its reads are all issued: there the wave waits for them and for the next
+    // step's loads, and after the barrier the buffers just read take the loads of the steps
+    // NA (tokens) and NB (weights) after it, spread over the last P items.
+    const int rd = (lane & 15) * kRowBytes + ((lane >> 4) ^ (lane & 7)) * 16;
+    const uint8_t *const ra = lds + wm * HB * 16 * kRowBytes;
+    const uint8_t *const rb = lds + C::kBBase + wn * (kGateUp ? 32 : 64) * kRowBytes;
+    bf16x8_t wf[2][4], tf[R];
+    auto read_item = [&](int j, int ba, int bb) {
+        const int kb = j / HB, sl = rd ^ (kb * 64);
+        if (j % HB == 0) {
 #pragma unroll
-            for (int m = 0; m < kMBlocks; ++m)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int tr = m * 16 + 4 * (lane >> 4) + r;
-                    if (tr >= rows) continue;
-#pragma unroll
-                    for (int nb = 0; nb < kNB / 2; ++nb) {
-                        const int c = wv * 8 * kNB + 16 * nb + (lane & 15);
-                        mine[tr * kCols + c] = acc[m][nb][r];
-                        mine[tr * kCols + kGuCols + c] = acc[m][nb + kNB / 2][r];
-                    }
-                }
-            return;
-        }
-    }
-    const int P = g.off[g.n];
-#pragma unroll
-    for (int m = 0; m < kMBlocks; ++m) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int tr = m * 16 + 4 * (lane >> 4) + r;
-            if (tr >= rows) continue;
-            if constexpr (kGateUp) {
-#pragma unroll
-                for (int nb = 0; nb < kNB / 2; ++nb) {
-                    const float gv = acc[m][nb][r], uv = acc[m][nb + kNB / 2][r];
-                    const float hv = gv / (1.0f + expf(-gv)) * uv;
-                    g.h[(size_t)(row0 + tr) * g.f + nt * kGuCols + wv * 8 * kNB + 16 * nb + (lane & 15)] = f2bf(hv);
-                }
-            } else {
-                float *dst = g.yp + ((size_t)ks * P + row0 + tr) * g.d + nt * (kWaves * 16 * kNB) + wv * 16 * kNB +
-                             (lane & 15);
-#pragma unroll
-                for (int nb = 0; nb < kNB; ++nb) dst[16 * nb] = acc[m][nb][r];
+            for (int nb = 0; nb < 4; ++nb) {
+                const int o = kGateUp ? (nb >> 1) * kGuCols + (nb & 1) * 16 : nb * 16;
+                wf[kb][nb] = *reinterpret_cast<const bf16x8_t *>(rb + bb * kBBytes + o * kRowBytes + sl);
             }
         }
+        tf[j % R] = *reinterpret_cast<const bf16x8_t *>(ra + ba * C::kABytes + (j % HB) * 16 * kRowBytes + sl);
+    };
+    auto mma = [&](int j, const bf16x8_t t) {
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+            acc[j % HB][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j / HB][nb], t, acc[j % HB][nb], 0, 0, 0);
+    };
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        if (q >= nsteps) continue;
+        if (q < NA)
+#pragma unroll
+            for (int i = 0; i < C::kALoads; ++i) load_a(i, q, q);
+#pragma unroll
+        for (int i = 0; i < kBLoads; ++i) load_b(i, q, q);
+    }
+    if (nsteps >= NB) wait_and_barrier<(NA - 1) * C::kALoads + (NB - 1) * kBLoads>();
+    else wait_and_barrier<0>();
+#pragma unroll
+    for (int j = 0; j < P; ++j) read_item(j, 0, 0);
+    int s = 0, ba = 0, bb = 0;
+    // One step. Steps that still have all loads to issue have no branch in them.
+    enum { kSteady, kDrain, kFinal };
+    auto step = [&](auto mode) {
+        constexpr bool kLast = decltype(mode)::value == kFinal, kFull = decltype(mode)::value == kSteady;
+        const int na = ba + 1 == NA ? 0 : ba + 1, nb = bb + 1 == NB ? 0 : bb + 1;
+#pragma unroll
+        for (int j = 0; j < kItems; ++j) {
+            const int at = j - (kItems - P);   // items since the hand-over
+            if (at == 0 && !kLast) {
+                if (kFull || s + NB - 1 < nsteps) wait_and_barrier<C::kKeep>();
+                else wait_and_barrier<0>();
+            }
+            if (at >= 0 && !kLast) {
+                constexpr int kEach = (C::kLoads + P - 1) / P;
+#pragma unroll
+                for (int i = at * kEach; i < (at + 1) * kEach && i < C::kLoads; ++i) {
+                    if (i < C::kALoads) {
+                        if (kFull || s + NA < nsteps) load_a(i, s + NA, ba);
+                    } else if (kFull || s + NB < nsteps) {
+                        load_b(i - C::kALoads, s + NB, bb);
+                    }
+                }
+            }
+            const bf16x8_t t = tf[j % R];
+            if (at < 0) read_item(j + P, ba, bb);
+            else if (!kLast) read_item(j + P - kItems, na, nb);
+            mma(j, t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        ++s;
+        ba = na;
+        bb = nb;
+    };
+    while (s + NB < nsteps) step(std::integral_constant<int, kSteady>{});
+    while (s + 1 < nsteps) step(std::integral_constant<int, kDrain>{});
+    step(std::integral_constant<int, kFinal>{});
+
+    // result r of a 16x16 block: weight row 4 (lane / 16) + r, token lane % 16
+    const int c4 = 4 * (lane >> 4);
+#pragma unroll
+    for (int m = 0; m < HB; ++m) {
+        const int tr = (wm * HB + m) * 16 + (lane & 15);
+        if (tr >= rows) continue;
+        if (part) {
+            float *dst = part + (size_t)tr * kTileN + c4;
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) {
+                const int col = kGateUp ? (nb >> 1) * kGuCols + wn * 32 + (nb & 1) * 16 : wn * 64 + nb * 16;
+                *reinterpret_cast<floatx4_t *>(dst + col) = acc[m][nb];
+            }
+        } else if constexpr (kGateUp) {
+            uint16_t *dst = g.h + (size_t)(row0 + tr) * g.f + nt * kGuCols + wn * 32 + c4;
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+                const floatx4_t gv = acc[m][nb], uv = acc[m][nb + 2];
+                uint2 o;
+                o.x = swiglu_bf(gv[0], uv[0]) | ((uint32_t)swiglu_bf(gv[1], uv[1]) << 16);
+                o.y = swiglu_bf(gv[2], uv[2]) | ((uint32_t)swiglu_bf(gv[3], uv[3]) << 16);
+                *reinterpret_cast<uint2 *>(dst + nb * 16) = o;
+            }
+        } else {
+            const int col0 = nt * kTileN + wn * 64 + c4;
+            float *dst = g.y + (size_t)(row0 + tr) * g.d + col0;
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+                if (col0 + nb * 16 < g.d) *reinterpret_cast<floatx4_t *>(dst + nb * 16) = acc[m][nb];
+        }
+    }
+}
+
+// kOnce: the weights are read about once (nontemporal loads).
+template <bool kGateUp, bool kOnce>
+__global__ __launch_bounds__(kGemmThreads) void k_moe_gemm(GemmArgs g)
+{
+    __shared__ __align__(1024) uint8_t lds[kLdsBytes];
+    const int lane = threadIdx.x & 63;
+    const int xcd = blockIdx.x % kXcds;
+    const TilePlan p = g.plan[xcd];
+    const int nunits = p.full + (p.units - p.full) * p.s;
+    const int nsteps = (kGateUp ? g.d : g.f) / kBK;
+    int tbase[MOE_MAX_EXPERTS / 64];   // first tile of experts lane, lane + 64, ...
+#pragma unroll
+    for (int i = 0; i < MOE_MAX_EXPERTS / 64; ++i) {
+        const int e = lane + 64 * i;
+        tbase[i] = e < g.n ? g.toff[e] * g.ntiles : 0x7fffffff;
+    }
+    for (int u = blockIdx.x / kXcds; u < nunits; u += g.slots) {
+        int t = u, ks = 0, parts = 1;
+        float *part = nullptr;
+        if (u >= p.full) {
+            const int v = u - p.full;
+            t = p.full + v / p.s;
+            ks = v % p.s;
+            parts = p.s;
+            part = g.part + ((size_t)xcd * g.maxparts + v) * g.prows * kTileN;
+        }
+        t += p.u0;
+        int e = -1;   // the last expert whose first tile is at or before t
+#pragma unroll
+        for (int i = 0; i < MOE_MAX_EXPERTS / 64; ++i) e += __popcll(__ballot(tbase[i] <= t));
+        const int o0 = g.off[e], c = g.off[e + 1] - o0;
+        t -= g.toff[e] * g.ntiles;
+        const int m = tiles_of(c), mt = t % m, nt = t / m;
+        const int r0 = tile_row(c, mt), row0 = o0 + r0, rows = tile_row(c, mt + 1) - r0;
+        const int k0 = nsteps * ks / parts, kn = nsteps * (ks + 1) / parts - k0;
+        // An expert's N tiles run side by side. With one M tile each walks its weights from a
+        // start of its own, so that they read different columns at a time (neighbours 256
+        // bytes apart: Mixtral-shaped 512-token layer 554 -> 532 us, 7 steps apart 535); with
+        // more, the tiles that share weights or tokens stay in step for the L2.
+        const int start = m == 1 ? (int)((unsigned)(nt * kStagger) % (unsigned)kn) : 0;
+        switch ((rows + 31) >> 5) {
+#define MOE_HB_CASE(N) \
+    case N: gemm_tile<kGateUp, kOnce, N>(g, lds, e, row0, rows, nt, k0, kn, start, part); break;
+            MOE_HB_CASE(1) MOE_HB_CASE(2) MOE_HB_CASE(3) MOE_HB_CASE(4)
+            MOE_HB_CASE(5) MOE_HB_CASE(6) MOE_HB_CASE(7) MOE_HB_CASE(8)
+#undef MOE_HB_CASE
+        default: break;
+        }
+        wait_and_barrier<0>();   // the last stage is read before the next tile's loads overwrite it
     }
 }
 
 // H of the gate/up tiles split over K: h = SiLU(sum of the g parts) * (sum of the u parts),
-// the parts added in order. Work group b: XCD b mod 8, then tile i of that XCD's partial
-// round and a block of 16 of its rows (the plan is recomputed from the expert offsets
-// exactly as the GEMM did); each thread takes 4 consecutive columns of 2 rows.
+// the parts added in order. Work group b: XCD b mod 8, then split tile i of that XCD and a
+// block of 16 of its rows; each thread takes 4 consecutive columns of 2 rows.
 constexpr int kTailRows = 16;
 __global__ __launch_bounds__(kThreads) void k_tail_combine(GemmArgs g)
 {
-    constexpr int kCols = 2 * kGuCols;   // g columns, then u columns
     constexpr int kQuads = kGuCols / 4;  // 4-column groups of the tile's columns
     const int xcd = blockIdx.x % kXcds;
     const int i = (blockIdx.x / kXcds) % g.slots;
     const int rb = blockIdx.x / kXcds / g.slots;
-    const TailPlan tp = tail_plan(g, xcd);
-    if (tp.s == 1 || i >= tp.r) return;
-    int e, mt, nt;
-    tail_tile(g, xcd, tp.R * g.slots + i, e, mt, nt);
-    const int row0 = g.off[e] + mt * kTileM;
-    const int rows = min(kTileM, g.off[e + 1] - row0);
-    const float *p0 = g.part + ((size_t)xcd * g.slots + (size_t)i * tp.s) * kTileM * kCols;
+    const TilePlan p = g.plan[xcd];
+    if (i >= p.units - p.full) return;
+    int t = p.u0 + p.full + i;
+    int lo = 0, hi = g.n - 1;   // the last expert whose first tile is at or before t
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (g.toff[mid] * g.ntiles <= t) lo = mid;
+        else hi = mid - 1;
+    }
+    const int o0 = g.off[lo], c0 = g.off[lo + 1] - o0;
+    t -= g.toff[lo] * g.ntiles;
+    const int m = tiles_of(c0), mt = t % m, nt = t / m;
+    const int r0 = tile_row(c0, mt), row0 = o0 + r0, rows = tile_row(c0, mt + 1) - r0;
+    const float *p0 = g.part + ((size_t)xcd * g.maxparts + (size_t)i * p.s) * g.prows * kTileN;
     for (int c = threadIdx.x; c < kTailRows * kQuads; c += kThreads) {
         const int tr = rb * kTailRows + c / kQuads, col = (c % kQuads) * 4;
         if (tr >= rows) continue;
         float4 gv = make_float4(0.f, 0.f, 0.f, 0.f), uv = gv;
-        for (int j = 0; j < tp.s; ++j) {
-            const float *pj = p0 + (size_t)j * kTileM * kCols + tr * kCols + col;
+        for (int j = 0; j < p.s; ++j) {
+            const float *pj = p0 + ((size_t)j * g.prows + tr) * kTileN + col;
             const float4 a = *reinterpret_cast<const float4 *>(pj);
-            const float4 b = *reinterpret_cast<const float4 *>(pj + kCols / 2);
+            const float4 b = *reinterpret_cast<const float4 *>(pj + kGuCols);
             gv.x += a.x; gv.y += a.y; gv.z += a.z; gv.w += a.w;
             uv.x += b.x; uv.y += b.y; uv.z += b.z; uv.w += b.w;
         }
         uint2 o;
-        o.x = f2bf(gv.x / (1.0f + expf(-gv.x)) * uv.x) | ((uint32_t)f2bf(gv.y / (1.0f + expf(-gv.y)) * uv.y) << 16);
-        o.y = f2bf(gv.z / (1.0f + expf(-gv.z)) * uv.z) | ((uint32_t)f2bf(gv.w / (1.0f + expf(-gv.w)) * uv.w) << 16);
+        o.x = swiglu_bf(gv.x, uv.x) | ((uint32_t)swiglu_bf(gv.y, uv.y) << 16);
+        o.y = swiglu_bf(gv.z, uv.z) | ((uint32_t)swiglu_bf(gv.w, uv.w) << 16);
         *reinterpret_cast<uint2 *>(g.h + (size_t)(row0 + tr) * g.f + nt * kGuCols + col) = o;
     }
 }
 
-// OUT[t][i] = sum_r w[t][r] * sum_s Yp[s][pos[t*k+r]][i], four consecutive i per thread;
-// work group b covers token b / nparts, columns (b mod nparts) * 1024 ...
-__global__ __launch_bounds__(kThreads) void k_prefill_combine(const float *yp, const int32_t *pos, const float *w,
-                                                              int k, int d, int P, int ksplit, int nparts, float *out)
+// OUT[t][i] = sum_r w[t][r] * y of pair (t, r), four consecutive i per thread. The y of a
+// tile split over K is the sum of its parts, in order; of any other tile, the GEMM's output.
+// Work group b covers token b / nparts, columns (b mod nparts) * 1024 ...
+__global__ __launch_bounds__(kThreads) void k_prefill_combine(GemmArgs g, const int32_t *idx, const int32_t *pos,
+                                                              const float *w, int k, int nparts, float *out)
 {
     const int t = blockIdx.x / nparts;
     const int i = ((blockIdx.x % nparts) * kThreads + threadIdx.x) * 4;
-    if (i >= d) return;
+    if (i >= g.d) return;
+    const int U = g.toff[g.n] * g.ntiles;
+    const int nt = i / kTileN;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int r = 0; r < k; ++r) {
-        const int pr = pos[t * k + r];
+        const int e = idx[t * k + r], pr = pos[t * k + r];
+        const int o0 = g.off[e], c = g.off[e + 1] - o0;
+        const int mt = tile_of_row(c, pr - o0);
+        const int u = g.toff[e] * g.ntiles + nt * tiles_of(c) + mt;
+        const int xcd = (int)(((int64_t)kXcds * u + kXcds - 1) / U);   // the run that holds tile u
+        const TilePlan p = g.plan[xcd];
+        const int v = u - p.u0 - p.full;
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int q = 0; q < ksplit; ++q) {
-            const float4 v = *reinterpret_cast<const float4 *>(yp + ((size_t)q * P + pr) * d + i);
-            s.x += v.x;
-            s.y += v.y;
-            s.z += v.z;
-            s.w += v.w;
+        if (v < 0) {
+            s = *reinterpret_cast<const float4 *>(g.y + (size_t)pr * g.d + i);
+        } else {
+            const float *src = g.part + (((size_t)xcd * g.maxparts + (size_t)v * p.s) * g.prows + (pr - o0 - tile_row(c, mt))) *
+                                            kTileN + i % kTileN;
+            for (int q = 0; q < p.s; ++q) {
+                const float4 a = *reinterpret_cast<const float4 *>(src + (size_t)q * g.prows * kTileN);
+                s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
+            }
         }
         const float wr = w[t * k + r];
         acc.x = fmaf(wr, s.x, acc.x);
@@ -563,28 +585,24 @@ __global__ __launch_bounds__(kThreads) void k_prefill_combine(const float *yp, c
         acc.z = fmaf(wr, s.z, acc.z);
         acc.w = fmaf(wr, s.w, acc.w);
     }
-    *reinterpret_cast<float4 *>(out + (size_t)t * d + i) = acc;
+    *reinterpret_cast<float4 *>(out + (size_t)t * g.d + i) = acc;
 }
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// K splits of the down GEMM: four when each part is still a whole number of K steps.
-int down_splits(int f) { return f % (kMaxDownSplits * kBK) == 0 ? kMaxDownSplits : 2; }
-
 struct PrefillWs {
     uint16_t *xb;
-    int32_t *idx, *off, *perm, *pos;
+    int32_t *idx, *off, *tok, *pos, *toff;
     float *w;
     uint16_t *h;
-    float *yp;
-    float *part;   // gate/up tail partial sums (expert-per-XCD layout only)
+    TilePlan *plan;
+    float *y;
+    float *gu_part, *dn_part;   // gate/up part buffers (y is written later), down part buffers
+    int gu_parts, dn_parts;     // their number per XCD
 };
 
-// Few (token, expert) pairs per expert: every expert's items are spread over all XCDs.
-bool spread_layout(int n, int k, int T) { return (int64_t)T * k < (int64_t)kSpreadTokens * n; }
-
-// fp32 (g, u) partial sums of the gate/up tiles split over K: [8][kMaxTailSlots][kTileM][2 * 128]
-constexpr size_t kPartBytes = (size_t)kXcds * kMaxTailSlots * kTileM * 2 * kGuCols * sizeof(float);
+// Rows of a part buffer: an expert has at most T tokens.
+int part_rows(int T) { return std::min(T, kTileM); }
 
 size_t layout(int d, int f, int n, int k, int T, uint8_t *base, PrefillWs *ws)
 {
@@ -599,21 +617,35 @@ size_t layout(int d, int f, int n, int k, int T, uint8_t *base, PrefillWs *ws)
     uint8_t *idx = take(P * 4);
     uint8_t *w = take(P * 4);
     uint8_t *off = take((size_t)(n + 1) * 4);
-    uint8_t *perm = take(P * 4);
+    uint8_t *tok = take(P * 4);
     uint8_t *pos = take(P * 4);
     uint8_t *h = take(P * f * 2);
-    uint8_t *yp = take((size_t)kMaxDownSplits * P * d * 4);
-    uint8_t *part = take(spread_layout(n, k, T) ? 0 : kPartBytes);
+    // fp32 sums: y, and part buffers in what is left of four times its size (plus 48 MiB
+    // from 64 tokens per expert on, where a part buffer has many rows); fewer part buffers
+    // only mean fewer K splits
+    const size_t sums = o;
+    take((size_t)4 * P * d * 4);
+    take((int64_t)T * k < (int64_t)64 * n ? 0 : (size_t)48 << 20);
     if (ws) {
         ws->xb = reinterpret_cast<uint16_t *>(xb);
         ws->idx = reinterpret_cast<int32_t *>(idx);
         ws->w = reinterpret_cast<float *>(w);
         ws->off = reinterpret_cast<int32_t *>(off);
-        ws->perm = reinterpret_cast<int32_t *>(perm);
+        ws->tok = reinterpret_cast<int32_t *>(tok);
         ws->pos = reinterpret_cast<int32_t *>(pos);
         ws->h = reinterpret_cast<uint16_t *>(h);
-        ws->yp = reinterpret_cast<float *>(yp);
-        ws->part = reinterpret_cast<float *>(part);
+        size_t at = sums;
+        ws->toff = reinterpret_cast<int32_t *>(base + at);
+        at += align256((size_t)(n + 1) * 4);
+        ws->plan = reinterpret_cast<TilePlan *>(base + at);
+        at += align256(sizeof(TilePlan) * 2 * kXcds);
+        const size_t set = (size_t)kXcds * part_rows(T) * kTileN * 4;   // one buffer on every XCD
+        ws->gu_part = reinterpret_cast<float *>(base + at);
+        ws->gu_parts = (int)std::min<size_t>(kMaxParts, (o - at) / set);
+        ws->y = reinterpret_cast<float *>(base + at);
+        at += align256(P * d * 4);
+        ws->dn_part = reinterpret_cast<float *>(base + at);
+        ws->dn_parts = (int)std::min<size_t>(kMaxParts, (o - at) / set);
     }
     return o;
 }
@@ -631,81 +663,79 @@ hipError_t launch_prefill(const PrefillPlan &P, const float *X, float *OUT, int3
     float *w_d = w ? w : ws.w;
     hipError_t e;
     if ((e = launch_router(X, P.wr, P.T, P.d, P.n, P.k, idx_d, w_d, s)) != hipSuccess) return e;
-    const int npairs = P.T * P.k;
+    const int slots = std::max(1, device_cu_count() / kXcds);
+
+    GroupArgs ga{};
+    ga.idx = idx_d;
+    ga.npairs = P.T * P.k;
+    ga.n = P.n;
+    ga.k = P.k;
+    ga.off = ws.off;
+    ga.toff = ws.toff;
+    ga.tok = ws.tok;
+    ga.pos = ws.pos;
+    ga.plan = ws.plan;
+    ga.ntiles[0] = P.f / kGuCols;
+    ga.ntiles[1] = (P.d + kTileN - 1) / kTileN;
+    ga.nsteps[0] = P.d / kBK;
+    ga.nsteps[1] = P.f / kBK;
+    ga.maxparts[0] = ws.gu_parts;
+    ga.maxparts[1] = ws.dn_parts;
+    ga.slots = slots;
+    ga.x = X;
+    ga.xb = ws.xb;
+    ga.n8 = (int64_t)P.T * P.d / 8;
+    const int cast_blocks = (int)std::min<int64_t>((ga.n8 + kGroupThreads - 1) / kGroupThreads, 1024);
     (void)hipGetLastError();
-    const int64_t n8 = (int64_t)P.T * P.d / 8;
-    const int cast_blocks = (int)std::min<int64_t>((n8 + kGroupThreads - 1) / kGroupThreads, 1024);
-    hipLaunchKernelGGL(k_group, dim3(1 + cast_blocks), dim3(kGroupThreads), 0, s, idx_d, npairs, P.n, ws.off, ws.perm,
-                       ws.pos, X, ws.xb, n8);
+    hipLaunchKernelGGL(k_group, dim3(1 + cast_blocks), dim3(kGroupThreads), 0, s, ga);
     if ((e = hipGetLastError()) != hipSuccess) return e;
 
     GemmArgs g{};
     g.pool = P.pool;
     g.slab_stride = P.slab_stride;
     g.off = ws.off;
-    g.perm = ws.perm;
+    g.toff = ws.toff;
+    g.tok = ws.tok;
     g.n = P.n;
-    g.k = P.k;
     g.d = P.d;
     g.f = P.f;
-    g.mtiles = (P.T + kTileM - 1) / kTileM;
+    g.slots = slots;
+    g.prows = part_rows(P.T);
     g.h = ws.h;
-    g.yp = ws.yp;
-    const int groups = (P.n + kXcds - 1) / kXcds;
-    // With few tokens per expert most experts are idle or nearly so, and keeping an
-    // expert on one XCD would leave the others without work; spread its tiles instead.
-    g.spread = spread_layout(P.n, P.k, P.T);
-    auto grid_of = [&](const GemmArgs &a) {
-        return g.spread ? P.n * a.mtiles * a.ntiles * a.ksplit : kXcds * a.per_xcd;
-    };
+    g.y = ws.y;
 
-    // gate/up: each work group covers 128 columns of H (128 W1 rows + the same 128 W3 rows), K = d
     g.a = ws.xb;
-    g.ntiles = P.f / kGuCols;
-    g.ksplit = 1;
-    g.per_xcd = groups * g.mtiles * g.ntiles * g.ksplit;
-    // Tail splitting (expert-per-XCD layout): the rounds of resident work groups per XCD
-    // decide which tiles are split.
-    static std::atomic<int> gu_occ_cache{-1};   // concurrent first calls store the same value
-    int gu_occ = gu_occ_cache.load(std::memory_order_relaxed);
-    if (gu_occ < 0) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&gu_occ, k_moe_gemm<true, 3, kGuNB, kGWaves>, kGWaves * 64,
-                                                         0) != hipSuccess ||
-            gu_occ < 1) {
-            (void)hipGetLastError();
-            gu_occ = 0;
-        }
-        gu_occ_cache.store(gu_occ, std::memory_order_relaxed);
-    }
-    const int slots = std::min(kMaxTailSlots, gu_occ * device_cu_count() / kXcds);
-    g.tail = !g.spread && slots >= 2;
-    g.slots = g.tail ? slots : 0;
-    g.part = ws.part;
-    // with tail splitting a work group takes a live tile or a K part of one: at most the
-    // live tiles plus one round of parts
-    const int gu_per_xcd = g.tail ? g.per_xcd + g.slots : g.per_xcd;
-    const int gu_grid = g.spread ? grid_of(g) : kXcds * gu_per_xcd;
-    hipLaunchKernelGGL((k_moe_gemm<true, 3, kGuNB, kGWaves>), dim3(gu_grid), dim3(kGWaves * 64), 0, s, g);
+    g.plan = ws.plan;
+    g.ntiles = ga.ntiles[0];
+    g.maxparts = ws.gu_parts;
+    g.part = ws.gu_part;
+    // Below one full M tile per expert on average the weights go by once and are loaded
+    // nontemporally (Mixtral-shaped 512 tokens: 575 -> 532 us, Phi 27 tokens: 415 -> 364 us);
+    // from there on M tiles share them through the caches (4096 tokens: 2545 us, nontemporal
+    // 2670 us; at 256 tokens per expert the two are within 2 %).
+    const bool once = (int64_t)P.T * P.k < (int64_t)kTileM * P.n;
+    const dim3 grid(kXcds * slots), block(kGemmThreads);
+    if (once) hipLaunchKernelGGL((k_moe_gemm<true, true>), grid, block, 0, s, g);
+    else hipLaunchKernelGGL((k_moe_gemm<true, false>), grid, block, 0, s, g);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (g.tail) {
-        hipLaunchKernelGGL(k_tail_combine, dim3(kXcds * g.slots * (kTileM / kTailRows)), dim3(kThreads), 0, s, g);
+    if (g.maxparts > 1) {
+        const int row_blocks = (g.prows + kTailRows - 1) / kTailRows;
+        hipLaunchKernelGGL(k_tail_combine, dim3(kXcds * slots * row_blocks), dim3(kThreads), 0, s, g);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
 
-    // down: 256 (or 128) output rows per work group, K = f split in 4 (or 2) parts
-    g.tail = 0;
     g.a = ws.h;
-    g.ksplit = down_splits(P.f);
-    const bool wide = P.d % 256 == 0;
-    g.ntiles = P.d / (wide ? 256 : 128);
-    g.per_xcd = groups * g.mtiles * g.ntiles * g.ksplit;
-    if (wide) hipLaunchKernelGGL((k_moe_gemm<false, 3, kDnNB, kGWaves>), dim3(grid_of(g)), dim3(kGWaves * 64), 0, s, g);
-    else hipLaunchKernelGGL((k_moe_gemm<false, 3, kDnNB / 2, kGWaves>), dim3(grid_of(g)), dim3(kGWaves * 64), 0, s, g);
+    g.plan = ws.plan + kXcds;
+    g.ntiles = ga.ntiles[1];
+    g.maxparts = ws.dn_parts;
+    g.part = ws.dn_part;
+    if (once) hipLaunchKernelGGL((k_moe_gemm<false, true>), grid, block, 0, s, g);
+    else hipLaunchKernelGGL((k_moe_gemm<false, false>), grid, block, 0, s, g);
     if ((e = hipGetLastError()) != hipSuccess) return e;
 
     const int nparts = (P.d + 4 * kThreads - 1) / (4 * kThreads);
-    hipLaunchKernelGGL(k_prefill_combine, dim3(P.T * nparts), dim3(kThreads), 0, s, ws.yp, ws.pos, w_d, P.k, P.d,
-                       npairs, g.ksplit, nparts, OUT);
+    hipLaunchKernelGGL(k_prefill_combine, dim3(P.T * nparts), dim3(kThreads), 0, s, g, idx_d, ws.pos, w_d, P.k, nparts,
+                       OUT);
     return hipGetLastError();
 }
 

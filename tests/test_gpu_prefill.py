@@ -148,3 +148,38 @@ def test_prefill_empty_and_invalid():
     with pytest.raises(moe.MoeError):
         moe.prefill_forward(torch.zeros((4, 200), device="cuda"), torch.zeros((n, 200), device="cuda"), pool,
                             200, f, n, k, out, ws)                # d not a multiple of 128
+
+
+# One expert, so the tokens per tile are T's own: the edges of the tile heights (32-row
+# blocks, 1 to 8 of them, and two or more tiles of uneven height), K loops shorter than the
+# load rings (d or f = 128: two steps), the half N tile of a d that is an odd multiple of
+# 128, K splits of a whole GEMM (2048, 1024) and weights shared by many tiles.
+_EDGES = [1, 16, 17, 32, 33, 64, 65, 97, 129, 160, 161, 193, 225, 256, 257, 288, 513, 545]
+
+
+@pytest.mark.parametrize("d,f,T", [(128, 128, T) for T in _EDGES + [2500]] + [(384, 256, T) for T in _EDGES + [2500]] +
+                         [(2048, 1024, T) for T in _EDGES])
+def test_prefill_tile_edges(d, f, T):
+    torch = torch_cuda()
+    say("prefill tile", d, f, T)
+    slab = synth.expert_slab(77 + d, d, f, None)
+    X = synth.iid_states(5 + T, T, d)
+    out, idx, w = _run(torch, X, synth.router_weights(9, 1, d), _pool_np(torch, [slab], d, f), d, f, 1, 1)
+    assert np.all(idx == 0) and np.all(w == 1.0)
+    # bf16 activations as in _bf16_activation_ref, all tokens at once
+    W = synth.bf16_to_f32(slab).astype(np.float64)
+    xb = synth.bf16_to_f32(synth.bf16_bits(X)).astype(np.float64)
+    g, u = xb @ W[:f * d].reshape(f, d).T, xb @ W[f * d:2 * f * d].reshape(f, d).T
+    h = g / (1.0 + np.exp(-g)) * u
+    hb = synth.bf16_to_f32(synth.bf16_bits(h.astype(np.float32))).astype(np.float64)
+    w2 = W[2 * f * d:].reshape(d, f)
+    ref = hb @ w2.T
+    rms = np.sqrt(np.mean(ref ** 2, axis=1))
+    # Bound: fp32 sums of up to 2048 terms in any order stay within 2e-5 RMS (5e-7 seen).
+    # An h within the fp32 error of a rounding midpoint (1e-5 (1 + |g|)(1 + |u|) covers it)
+    # may round to the other side, which moves the outputs by one bf16 ulp of it times W2.
+    ulp = np.exp2(np.floor(np.log2(np.abs(h) + 1e-30)) - 7)
+    near = np.abs(np.abs(h - hb) - ulp / 2) <= 1e-5 * (1 + np.abs(g)) * (1 + np.abs(u))
+    flip = (near * ulp) @ np.abs(w2).T
+    worst = np.max(np.abs(out - ref) - flip, axis=1) / rms
+    assert np.all(worst <= 2e-5), (int(np.argmax(worst)), float(worst.max()))
