@@ -446,6 +446,126 @@ __global__ __launch_bounds__(kRouterBlock) void k_router(const float *X, const f
 }
 
 // ---------------------------------------------------------------------------
+// Batched router, TB tokens per work group: the tokens are staged in LDS and a wave dots
+// four router rows at a time with all of them, lane l taking float4 chunks l, l + 64, ...
+// A router value is then loaded and widened to fp64 once per TB tokens and a token's value
+// once per four experts, where k_router widens both for every product. An item is a group
+// of four experts and one of S segments of K (S > 1 while there are fewer groups than
+// waves). The products are the exact fp64 ones and every expert's are added in the same
+// order, so equal rows give equal logits.
+// The widening (a quarter-rate operation) bounds it: 1500 tokens on 64 experts of d = 3584
+// take 39 us (k_router 71), 4096 tokens on 8 experts of d = 4096 25 us (k_router 41). Eight
+// experts a wave (44 us) or eight tokens a work group (37 and 29 us) need more registers
+// and LDS for little; the fp64 matrix instructions, half the vector units' rate here, took
+// 47 us.
+// ---------------------------------------------------------------------------
+constexpr int kRouterWaves = kRouterBlock / kWave;
+constexpr int kGroupExp = 4;
+
+// v[i] summed over the wave's lanes, for N (a power of two, at most 64) values at once: each
+// exchange halves the values a lane still carries. The sum of value i ends up in the lanes
+// whose top log2(N) lane bits, from bit 5 down, spell i.
+template <int N, int O = 32>
+__device__ __forceinline__ double wave_sums(const double (&v)[N], int lane)
+{
+    if constexpr (O == 0) {
+        return v[0];
+    } else if constexpr (N == 1) {
+        const double s[1] = {v[0] + __shfl_xor(v[0], O, kWave)};
+        return wave_sums<1, O / 2>(s, lane);
+    } else {
+        const bool up = lane & O;
+        double s[N / 2];
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {
+            const double give = up ? v[i] : v[i + N / 2], keep = up ? v[i + N / 2] : v[i];
+            s[i] = keep + __shfl_xor(give, O, kWave);
+        }
+        return wave_sums<N / 2, O / 2>(s, lane);
+    }
+}
+
+template <int TB>
+__global__ __launch_bounds__(kRouterBlock) void k_router_batch(const float *X, const float *Wr, int T, int d, int n, int k,
+                                                               int S, int32_t *idx, float *wout)
+{
+    extern __shared__ float4 xs[];                         // [TB][nch * 64], zero past the row
+    __shared__ double part[TB][MOE_MAX_EXPERTS];           // [token][segment][expert]
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = threadIdx.x >> 6;
+    const int t0 = blockIdx.x * TB;
+    const int nq = d >> 2, nch = (nq + kWave - 1) / kWave, np = nch * kWave;
+    const int groups = (n + kGroupExp - 1) / kGroupExp;
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+        const float4 *x4 = reinterpret_cast<const float4 *>(X + (size_t)min(t0 + t, T - 1) * d);
+        for (int q = threadIdx.x; q < np; q += kRouterBlock) xs[t * np + q] = q < nq ? x4[q] : make_float4(0, 0, 0, 0);
+    }
+    __syncthreads();
+    for (int it = wv; it < groups * S; it += kRouterWaves) {
+        const int g = it / S, sg = it - g * S;
+        const int c0 = nch * sg / S, c1 = nch * (sg + 1) / S;
+        const float4 *w4[kGroupExp];
+#pragma unroll
+        for (int e = 0; e < kGroupExp; ++e)
+            w4[e] = reinterpret_cast<const float4 *>(Wr + (size_t)min(g * kGroupExp + e, n - 1) * d);
+        double acc[TB * kGroupExp];
+#pragma unroll
+        for (int i = 0; i < TB * kGroupExp; ++i) acc[i] = 0.0;
+        float4 w[2][kGroupExp];
+        auto load = [&](int set, int c) {   // past the row: its last chunk, against zeros of x
+            const int q = min(min(c, c1 - 1) * kWave + lane, nq - 1);
+#pragma unroll
+            for (int e = 0; e < kGroupExp; ++e) w[set][e] = w4[e][q];
+        };
+        auto dot = [&](int set, int c) {
+            float4 xv[TB];
+#pragma unroll
+            for (int t = 0; t < TB; ++t) xv[t] = xs[t * np + c * kWave + lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                double wd[kGroupExp];
+#pragma unroll
+                for (int e = 0; e < kGroupExp; ++e) wd[e] = (&w[set][e].x)[i];
+#pragma unroll
+                for (int t = 0; t < TB; ++t) {
+                    const double xd = (&xv[t].x)[i];
+#pragma unroll
+                    for (int e = 0; e < kGroupExp; ++e)
+                        acc[t * kGroupExp + e] = fma(wd[e], xd, acc[t * kGroupExp + e]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if (c0 < c1) {
+            load(0, c0);
+            for (int c = c0; c < c1; c += 2) {
+                load(1, c + 1);
+                dot(0, c);
+                load(0, c + 2);
+                if (c + 1 < c1) dot(1, c + 1);
+            }
+        }
+        const double sum = wave_sums(acc, lane);
+        constexpr int kVals = TB * kGroupExp, kRep = kWave / kVals;   // lanes per value
+        const int i = lane / kRep;
+        if (lane % kRep == 0) part[i / kGroupExp][(sg * groups + g) * kGroupExp + i % kGroupExp] = sum;
+    }
+    __syncthreads();
+    if (S > 1) {   // n <= 28: the segments' sums, in order
+        for (int i = threadIdx.x; i < TB * groups * kGroupExp; i += kRouterBlock) {
+            const int t = i / (groups * kGroupExp), e = i - t * groups * kGroupExp;
+            double l = part[t][e];
+            for (int sg = 1; sg < S; ++sg) l += part[t][sg * groups * kGroupExp + e];
+            part[t][e] = l;
+        }
+        __syncthreads();
+    }
+    for (int t = wv; t < TB && t0 + t < T; t += kRouterWaves)
+        select_topk(part[t], n, k, lane, idx + (size_t)(t0 + t) * k, wout + (size_t)(t0 + t) * k, nullptr);
+}
+
+// ---------------------------------------------------------------------------
 // Single-token decode router over many work groups. Item (e, s) = expert e, segment s
 // (kRouteSeg floats) of its router row; wave `item` of the grid streams that segment
 // (four 16-byte loads per lane, all in flight at once) against the same slice of x and
@@ -759,6 +879,23 @@ void ffn_bind_workspace(FfnParams &p, void *ws, int max_jobs, int d, int f_max)
     p.smax = seg_count(f_max);
 }
 
+namespace {
+
+template <int TB>
+hipError_t launch_router_batch(const float *x, const float *wr, int T, int d, int n, int k, int32_t *idx, float *w,
+                               hipStream_t s)
+{
+    const int groups = (n + kGroupExp - 1) / kGroupExp;
+    const int S = groups >= kRouterWaves ? 1 : (kRouterWaves + groups - 1) / groups;
+    const size_t lds = (size_t)TB * ((d / 4 + kWave - 1) / kWave) * kWave * sizeof(float4);
+    clear_launch_error();
+    hipLaunchKernelGGL(k_router_batch<TB>, dim3((T + TB - 1) / TB), dim3(kRouterBlock), lds, s, x, wr, T, d, n, k, S, idx,
+                       w);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_router(const float *x, const float *wr, int T, int d, int n, int k, int32_t *idx,
                          float *w, hipStream_t s, RouteMailbox *mbox, float *x_host, int32_t seq,
                          const int32_t *row_src, int32_t *row_dst)
@@ -767,6 +904,15 @@ hipError_t launch_router(const float *x, const float *wr, int T, int d, int n, i
     if (T != 1) mbox = nullptr, x_host = nullptr, row_src = nullptr;
     if (!row_dst) row_src = nullptr;
     const int cpr = (d / 4 + kWave - 1) / kWave;
+    // Several tokens per work group once one token each would take the chip more than one
+    // round of work groups, or two while the router matrix is small: a lone work group of
+    // four tokens takes longer than one of one (3584 x 64: 24 against 20 us; 4096 x 8: 10
+    // against 8 us for 512 tokens). The tokens' LDS copy holds 64 KiB.
+    const int cus = device_cu_count();
+    if (T > 2 * cus || (T > cus && n > 16)) {
+        if (d <= 4096) return launch_router_batch<4>(x, wr, T, d, n, k, idx, w, s);
+        if (d <= 8192) return launch_router_batch<2>(x, wr, T, d, n, k, idx, w, s);
+    }
 #define MOE_CPR_CASE(N) \
     if (cpr <= N) return launch_router_cpr<N>(x, wr, T, d, n, k, idx, w, s, mbox, x_host, seq, row_src, row_dst);
     MOE_CPR_CASE(1) MOE_CPR_CASE(2) MOE_CPR_CASE(4) MOE_CPR_CASE(8) MOE_CPR_CASE(16) MOE_CPR_CASE(32)

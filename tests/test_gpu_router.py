@@ -52,6 +52,27 @@ def test_router_exact_ties():
         assert gw[0][0] == gw[0][1] == np.float32(0.5)
 
 
+# Batches of several tokens per work group: K split over segments (few experts, and more
+# segments than K chunks at d = 64), a K tail, expert groups and token groups that n and T do
+# not fill, the two-token form (d > 4096) and the largest n and k.
+@pytest.mark.parametrize("d,n,k,T", [(64, 5, 5, 1030), (264, 8, 1, 601), (4096, 8, 2, 530), (520, 17, 3, 259),
+                                     (3584, 64, 8, 300), (8192, 256, 16, 258), (4104, 30, 2, 513)])
+def test_router_batch_parity(d, n, k, T):
+    torch = torch_cuda()
+    say("router batch", d, n, k, T)
+    wr = synth.router_weights(synth.seed_for(2, "mixtral", "router", d, n), n, d)
+    wr[n - 1] = wr[0]                                   # an exact tie: the lower id first
+    X = synth.iid_states(synth.seed_for(2, "mixtral", "states", d, k), T, d)
+    gi, gw = _run(torch, X, wr, k)
+    for t in range(T):
+        router_parity(gi[t], gw[t], X[t], wr, k)
+        if n - 1 in gi[t]:
+            p = list(gi[t])
+            assert p.index(0) == p.index(n - 1) - 1 and gw[t][p.index(0)] == gw[t][p.index(n - 1)]
+    gi, gw = _run(torch, X, np.zeros((n, d), np.float32), k)
+    assert np.all(gi == np.arange(k)) and np.all(gw == np.float32(1.0 / k))
+
+
 def test_router_empty_batch_is_noop():
     torch = torch_cuda()
     import paper_2512_16473_amd as moe
