@@ -21,6 +21,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "moe_internal.h"
 #include "stream_ops.h"
@@ -33,7 +35,9 @@ using namespace stream_ops;
 constexpr int kTokThreads = 512;                         // 8 waves share the LDS copy
 constexpr int kTokWaves = kTokThreads / kWave;
 constexpr int kMaxPairs = MOE_MAX_TOKENS * MOE_MAX_TOPK_INTERNAL;   // 128
-constexpr int kDownRows = 128;                           // W2 rows per down work group
+constexpr int kRowCost = 4;                              // what a down row costs besides its pairs, in pairs
+constexpr size_t kDeepLds = (size_t)80 << 10;            // from here on one down work group fits a CU
+constexpr int kDownRows = 16;                            // W2 rows per down work group, at least
 
 static_assert(kMaxPairs <= kTokThreads, "one thread per (token, rank) pair");
 static_assert(kMaxPairs <= 2 * kWave, "a wave keeps a job's pair results in two registers");
@@ -109,56 +113,42 @@ struct TokJobs {
     int slot[kMaxPairs];        // job -> slot
     int first[kMaxPairs + 1];   // job -> its range in `pair`
     int pair[kMaxPairs];        // pair ids t*k + r grouped by job, ascending within a job
-    int lead[kMaxPairs];        // scratch: first pair with the same slot, -1 if skipped
 };
 
-// Every thread p < T*k takes one pair; all loops are over at most 128 entries.
-__device__ void build_jobs(const int32_t *slots, int npairs, int nslots, TokJobs &J)
+// The job table, by the first wave: lane l holds the slots of pairs l and l + 64; the job of
+// the first pair not yet placed takes every pair with its slot, found with two ballots. The
+// caller synchronises the work group before the table is read.
+__device__ __forceinline__ void build_jobs(const int32_t *slots, int npairs, int nslots, TokJobs &J)
 {
-    const int p = threadIdx.x;
-    int s = -1;
-    if (p < npairs) {
-        s = slots[p];
-        if (s < 0 || s >= nslots) s = -1;
-    }
-    if (p < kMaxPairs) J.lead[p] = -1;
-    __syncthreads();
-    if (p < npairs && s >= 0) {
-        int l = p;
-        for (int q = 0; q < p; ++q)
-            if (slots[q] == s) {   // the same valid slot (s is in range)
-                l = q;
-                break;
+    if (threadIdx.x < kWave) {
+        const int lane = threadIdx.x;
+        int s0 = lane < npairs ? slots[lane] : -1, s1 = lane + kWave < npairs ? slots[lane + kWave] : -1;
+        if (s0 >= nslots) s0 = -1;
+        if (s1 >= nslots) s1 = -1;
+        uint64_t m0 = __ballot(s0 >= 0), m1 = __ballot(s1 >= 0);
+        const uint64_t below = (1ull << lane) - 1;
+        int job = 0, start = 0;
+        while (m0 | m1) {
+            const int slot = m0 ? __builtin_amdgcn_readlane(s0, __builtin_ctzll(m0))
+                                : __builtin_amdgcn_readlane(s1, __builtin_ctzll(m1));
+            const uint64_t b0 = __ballot(s0 == slot), b1 = __ballot(s1 == slot);
+            const int n0 = __popcll(b0);
+            if (s0 == slot) J.pair[start + __popcll(b0 & below)] = lane;
+            if (s1 == slot) J.pair[start + n0 + __popcll(b1 & below)] = lane + kWave;
+            if (lane == 0) {
+                J.slot[job] = slot;
+                J.first[job] = start;
             }
-        J.lead[p] = l;
-    }
-    __syncthreads();
-    if (p < npairs && s >= 0) {
-        const int l = J.lead[p];
-        int start = 0, pos = 0, job = 0;
-        for (int q = 0; q < npairs; ++q) {
-            const int lq = J.lead[q];
-            if (lq < 0) continue;
-            start += lq < l;             // pairs of earlier jobs (jobs ordered by their lead)
-            pos += (lq == l && q < p);   // earlier pairs of this job
-            job += (lq == q && q < l);   // jobs led before this one
+            start += n0 + __popcll(b1);
+            ++job;
+            m0 &= ~b0;
+            m1 &= ~b1;
         }
-        J.pair[start + pos] = p;
-        if (l == p) {
-            J.slot[job] = s;
+        if (lane == 0) {
             J.first[job] = start;
+            J.njobs = job;
         }
     }
-    if (p == 0) {
-        int nj = 0, nv = 0;
-        for (int q = 0; q < npairs; ++q) {
-            nv += J.lead[q] >= 0;
-            nj += J.lead[q] == q;
-        }
-        J.njobs = nj;
-        J.first[nj] = nv;
-    }
-    __syncthreads();
 }
 
 struct TokParams {
@@ -265,84 +255,117 @@ __global__ __launch_bounds__(kTokThreads) void k_tok_gate_up(TokParams p)
 #undef MOE_TOK_DOT
 }
 
-// partial[p][s][r] = w_p * sum over segment s of W2_r h_p, for every pair p of a job.
-// Work group b: job b / (nseg * nchunk), segment, and kDownRows consecutive rows r; the
-// h segments of the job's pairs are staged in LDS. CPK = 16-byte chunks per lane of a
-// segment (seg <= CPK * 512).
-template <int CPK>
+// partial[p][s][r] = w_p * sum over segment s of W2_r h_p, for every pair p of a job. The
+// (job, segment, row) triples, in that order, are split into one contiguous share of equal
+// weight per resident work group (a row weighs its job's pairs and a constant: jobs with
+// several pairs are bound by the dot products, the others by the weight stream; with
+// rows alone 8 Mixtral-shaped tokens took 421 instead of 405 us). Where a share enters a
+// (job, segment), the group stages the h segments of the job's pairs in LDS while its first
+// rows are on their way, and streams its rows of that segment, kSets - 1 of them ahead: four
+// sets where the staging leaves one work group per CU (10 KB in flight per wave with two),
+// two where more groups share the CU. With one work group per 128 rows of a (job, segment),
+// each building the job table and staging before its first load, 8 fine-grained tokens (43
+// slabs) took 446 us, now 379; 8 Phi-shaped ones 250, now 242.
+// CPK = 16-byte chunks per lane of a segment (seg <= CPK * 512).
+template <int CPK, int kSets>
 __global__ __launch_bounds__(kTokThreads) void k_tok_down(TokParams p)
 {
     constexpr int kPitch = CPK * kWave;   // chunks per staged pair row in LDS
     __shared__ TokJobs J;
     extern __shared__ uint4 hs4[];        // hi parts [T][kPitch], then lo parts [T][kPitch]
     build_jobs(p.slots, p.T * p.k, p.nslots, J);
-    const int nchunk = (p.d + kDownRows - 1) / kDownRows;
-    const int job = blockIdx.x / (p.nseg * nchunk);
-    if (job >= J.njobs) return;
-    const int sgi = (blockIdx.x / nchunk) % p.nseg;
-    const int r0 = (blockIdx.x % nchunk) * kDownRows;
-    const int c0 = sgi * p.seg;
-    const int len = min(p.seg, p.f - c0);
-    const int nch = len >> 3;
-    const int q0 = J.first[job], np = J.first[job + 1] - q0;
-    const int lo_off = p.T * kPitch;
+    __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
-    const uint8_t *w2 = p.pool + (uint64_t)J.slot[job] * p.slab_stride + (uint64_t)2 * p.f * p.d * 2;
-    const int r1 = min(r0 + kDownRows, p.d);
-    // LDS holds the h segments of T pairs; a job has at most T (one per token) unless a
-    // token listed a slot twice, and then its pairs go through in groups of T.
-    for (int qc = 0; qc < np; qc += p.T) {
-        const int nq = min(p.T, np - qc);
-        if (qc) __syncthreads();   // the previous group's segments are no longer read
-        // chunks past the segment's end hold zeros (see k_tok_gate_up)
-        for (int i = threadIdx.x; i < nq * kPitch; i += kTokThreads) {
-            const int q = i / kPitch, e = i - q * kPitch;
-            if (e < nch) split8(p.h + (size_t)J.pair[q0 + qc + q] * p.f + c0 + e * 8, hs4 + i, hs4 + lo_off + i);
-            else hs4[i] = hs4[lo_off + i] = make_uint4(0, 0, 0, 0);
+    const int lo_off = p.T * kPitch;
+    // The (job, segment, row) triples weigh kRowCost plus the job's pairs; this group's
+    // share is [at, at_end) of the total weight, from row ceil(offset / weight) of a job on.
+    const int64_t rows = (int64_t)p.nseg * p.d;   // of a job
+    const int64_t total = (J.first[J.njobs] + (int64_t)kRowCost * J.njobs) * rows;
+    const int64_t at = total * blockIdx.x / gridDim.x, at_end = total * (blockIdx.x + 1) / gridDim.x;
+    int job = 0;
+    int64_t row = 0, row_end = 0;                 // of the job: this group's next and end
+    auto enter = [&](int j) {
+        const int64_t base = (J.first[j] + (int64_t)kRowCost * j) * rows;
+        const int64_t w = J.first[j + 1] - J.first[j] + kRowCost;
+        row = at <= base ? 0 : (at - base + w - 1) / w;
+        row_end = min(rows, (at_end - base + w - 1) / w);
+    };
+    if (at < at_end) {
+        while ((J.first[job + 1] + (int64_t)kRowCost * (job + 1)) * rows <= at) ++job;
+        enter(job);
+    }
+    for (bool staged = false;; staged = true) {
+        while (row >= row_end) {                  // uniform: the same in every thread
+            ++job;
+            if (job >= J.njobs || (J.first[job] + (int64_t)kRowCost * job) * rows >= at_end) return;
+            enter(job);
         }
-        __syncthreads();
-        // lane q < nq holds pair q's id and combine weight, and keeps its dot product;
-        // the stores follow the pair loop (see k_tok_gate_up)
-        const int pr_l = lane < nq ? J.pair[q0 + qc + lane] : 0;
-        const float w_l = lane < nq ? p.w[pr_l] : 0.f;
-        // rows r, r + 8, ... of this group, two register sets (the next row's segment in
-        // flight while this one is dotted); loads past the last row re-read it
-        uint4 a[2][CPK];
+        const int sgi = (int)(row / p.d);
+        const int r0 = (int)(row - (int64_t)sgi * p.d);
+        const int r1 = (int)min((int64_t)p.d, r0 + (row_end - row));
+        row += r1 - r0;
+        const int c0 = sgi * p.seg;
+        const int nch = min(p.seg, p.f - c0) >> 3;
+        const int q0 = J.first[job], np = J.first[job + 1] - q0;
+        const uint8_t *w2 = p.pool + (uint64_t)J.slot[job] * p.slab_stride + (uint64_t)2 * p.f * p.d * 2;
+        // LDS holds the h segments of T pairs; a job has at most T (one per token) unless a
+        // token listed a slot twice, and then its pairs go through in groups of T.
+        for (int qc = 0; qc < np; qc += p.T) {
+            const int nq = min(p.T, np - qc);
+            // rows r, r + 8, ... of the range, two register sets (the next row's segment in
+            // flight while this one is dotted); loads past the last row re-read it. The first
+            // row's are in flight while the segments are staged.
+            uint4 a[kSets][CPK];
 #define MOE_TOK_LOAD_ROW(set, rr)                                                                      \
-        do {                                                                                           \
-            const uint4 *row_ = reinterpret_cast<const uint4 *>(w2 + ((uint64_t)min((rr), r1 - 1) * p.f + c0) * 2); \
-            _Pragma("unroll") for (int c = 0; c < CPK; ++c) a[set][c] = stream_load(row_ + min(c * kWave + lane, nch - 1)); \
-        } while (0)
-#define MOE_TOK_DOT_ROW(set, rr)                                                                       \
-        do {                                                                                           \
-            const bool live_ = (rr) < r1;                                                              \
-            const int nl_ = live_ ? nq : 1;                                                            \
-            float o_ = 0.f;                                                                            \
-            int q = 0;                                                                                 \
             do {                                                                                       \
-                const uint4 *ht = hs4 + q * kPitch + lane;                                             \
-                float ah = 0.f, al = 0.f;                                                              \
-                _Pragma("unroll") for (int c = 0; c < CPK; ++c) {                                      \
-                    ah = dot8_bf(a[set][c], ht[c * kWave], ah);                                        \
-                    al = dot8_bf(a[set][c], ht[lo_off + c * kWave], al);                               \
-                }                                                                                      \
-                const float acc = wave_total(ah + al);                                                   \
-                if (lane == q) o_ = acc;                                                               \
-            } while (++q < nl_);                                                                       \
-            if (live_ && lane < nq) p.partial[((size_t)pr_l * p.nseg + sgi) * p.d + (rr)] = w_l * o_;  \
-        } while (0)
-        // uniform loop control without a mid-loop exit; a row past the end is dotted with
-        // one pair and not stored (see k_tok_gate_up)
-        int r = r0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        if (r < r1) MOE_TOK_LOAD_ROW(0, r);
-        for (; r < r1; r += 2 * kTokWaves) {
-            MOE_TOK_LOAD_ROW(1, r + kTokWaves);
-            MOE_TOK_DOT_ROW(0, r);
-            MOE_TOK_LOAD_ROW(0, r + 2 * kTokWaves);
-            MOE_TOK_DOT_ROW(1, r + kTokWaves);
-        }
+                const uint4 *row_ = reinterpret_cast<const uint4 *>(w2 + ((uint64_t)min((rr), r1 - 1) * p.f + c0) * 2); \
+                _Pragma("unroll") for (int c = 0; c < CPK; ++c) a[set][c] = stream_load(row_ + min(c * kWave + lane, nch - 1)); \
+            } while (0)
+#define MOE_TOK_DOT_ROW(set, rr)                                                                       \
+            do {                                                                                       \
+                const bool live_ = (rr) < r1;                                                          \
+                const int nl_ = live_ ? nq : 1;                                                        \
+                float o_ = 0.f;                                                                        \
+                int q = 0;                                                                             \
+                do {                                                                                   \
+                    const uint4 *ht = hs4 + q * kPitch + lane;                                         \
+                    float ah = 0.f, al = 0.f;                                                          \
+                    _Pragma("unroll") for (int c = 0; c < CPK; ++c) {                                  \
+                        ah = dot8_bf(a[set][c], ht[c * kWave], ah);                                    \
+                        al = dot8_bf(a[set][c], ht[lo_off + c * kWave], al);                           \
+                    }                                                                                  \
+                    const float acc = wave_total(ah + al);                                             \
+                    if (lane == q) o_ = acc;                                                           \
+                } while (++q < nl_);                                                                   \
+                if (live_ && lane < nq) p.partial[((size_t)pr_l * p.nseg + sgi) * p.d + (rr)] = w_l * o_; \
+            } while (0)
+            int r = r0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+            for (int u = 0; u < kSets - 1; ++u) MOE_TOK_LOAD_ROW(u, r + u * kTokWaves);
+            if (staged || qc) __syncthreads();   // the segments staged before are no longer read
+            // chunks past the segment's end hold zeros (see k_tok_gate_up)
+            for (int i = threadIdx.x; i < nq * kPitch; i += kTokThreads) {
+                const int q = i / kPitch, e = i - q * kPitch;
+                if (e < nch) split8(p.h + (size_t)J.pair[q0 + qc + q] * p.f + c0 + e * 8, hs4 + i, hs4 + lo_off + i);
+                else hs4[i] = hs4[lo_off + i] = make_uint4(0, 0, 0, 0);
+            }
+            __syncthreads();
+            // lane q < nq holds pair q's id and combine weight, and keeps its dot product;
+            // the stores follow the pair loop (see k_tok_gate_up)
+            const int pr_l = lane < nq ? J.pair[q0 + qc + lane] : 0;
+            const float w_l = lane < nq ? p.w[pr_l] : 0.f;
+            // uniform loop control without a mid-loop exit; a row past the end is dotted with
+            // one pair and not stored (see k_tok_gate_up)
+            for (; r < r1; r += kSets * kTokWaves) {
+#pragma unroll
+                for (int u = 0; u < kSets; ++u) {
+                    MOE_TOK_LOAD_ROW((u + kSets - 1) % kSets, r + (u + kSets - 1) * kTokWaves);
+                    MOE_TOK_DOT_ROW(u, r + u * kTokWaves);
+                }
+            }
 #undef MOE_TOK_LOAD_ROW
 #undef MOE_TOK_DOT_ROW
+        }
     }
 }
 
@@ -372,23 +395,21 @@ int seg_len_tok(int f)
 }
 
 // Allows `lds` bytes of dynamic LDS (beyond 64 KiB it has to be allowed per kernel;
-// gfx950 has 160 KiB per CU) and launches; grid <= 0: as many work groups as fit on the
-// device at once.
+// gfx950 has 160 KiB per CU) and launches as many work groups as fit on the device at
+// once, at most max_grid.
 template <typename K>
-hipError_t launch_dyn(K kernel, int grid, size_t lds, hipStream_t s, const TokParams &p)
+hipError_t launch_dyn(K kernel, int64_t max_grid, size_t lds, hipStream_t s, const TokParams &p)
 {
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
     (void)hipGetLastError();
-    if (grid <= 0) {
-        int occ = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, kTokThreads, lds) != hipSuccess || occ < 1) {
-            (void)hipGetLastError();
-            occ = 1;
-        }
-        grid = occ * device_cu_count();
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, kTokThreads, lds) != hipSuccess || occ < 1) {
+        (void)hipGetLastError();
+        occ = 1;
     }
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kTokThreads), lds, s, p);
+    const int64_t grid = std::min<int64_t>((int64_t)occ * device_cu_count(), max_grid);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kTokThreads), lds, s, p);
     return hipGetLastError();
 }
 
@@ -424,10 +445,9 @@ hipError_t launch_tokens(const float *x, const uint8_t *pool, uint64_t stride, i
     const int cpl = (d / 8 + kWave - 1) / kWave;
     // T rows of cpl * 64 chunks, each chunk 16 bytes of hi parts and 16 of lo parts
     const size_t lds_x = (size_t)T * cpl * kWave * 32;
-    const int gu_grid = 0;
     switch (cpl) {
 #define MOE_TOK_CPL(N) \
-    case N: e = launch_dyn(k_tok_gate_up<N>, gu_grid, lds_x, s, p); break;
+    case N: e = launch_dyn(k_tok_gate_up<N>, INT64_MAX, lds_x, s, p); break;
         MOE_TOK_CPL(1) MOE_TOK_CPL(2) MOE_TOK_CPL(3) MOE_TOK_CPL(4) MOE_TOK_CPL(5) MOE_TOK_CPL(6)
         MOE_TOK_CPL(7) MOE_TOK_CPL(8) MOE_TOK_CPL(9) MOE_TOK_CPL(10) MOE_TOK_CPL(11) MOE_TOK_CPL(12)
         MOE_TOK_CPL(13) MOE_TOK_CPL(14) MOE_TOK_CPL(15) MOE_TOK_CPL(16)
@@ -435,15 +455,17 @@ hipError_t launch_tokens(const float *x, const uint8_t *pool, uint64_t stride, i
     default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
-    // down: one work group per (job, segment, kDownRows rows); groups past the job count exit
-    const int nchunk = (d + kDownRows - 1) / kDownRows;
-    const int dn_grid = max_jobs * p.nseg * nchunk;
+    // down: one round of resident work groups, fewer where they would get under kDownRows rows
+    const int64_t dn_grid = ((int64_t)max_jobs * p.nseg * d + kDownRows - 1) / kDownRows;
     const int cpk = (p.seg / 8 + kWave - 1) / kWave;
     const size_t lds_h = (size_t)T * cpk * kWave * 32;
+    const bool deep = lds_h >= kDeepLds;
     if (dn_grid > 0) {
         switch (cpk) {
 #define MOE_TOK_CPK(N) \
-    case N: e = launch_dyn(k_tok_down<N>, dn_grid, lds_h, s, p); break;
+    case N: \
+        e = deep ? launch_dyn(k_tok_down<N, 4>, dn_grid, lds_h, s, p) : launch_dyn(k_tok_down<N, 2>, dn_grid, lds_h, s, p); \
+        break;
             MOE_TOK_CPK(1) MOE_TOK_CPK(2) MOE_TOK_CPK(3) MOE_TOK_CPK(4) MOE_TOK_CPK(5) MOE_TOK_CPK(6)
             MOE_TOK_CPK(7) MOE_TOK_CPK(8)
 #undef MOE_TOK_CPK

@@ -74,6 +74,30 @@ def test_tokens_parity(d, f, nslots, T, k):
         assert_close(y[t], e, f"tokens d={d} f={f} t={t} slots={list(slots[t])}")
 
 
+# The down kernel's shares: four register sets (at least 80 KiB of staged h: 5 to 8 chunks a
+# lane at T = 8) and two, ragged segments, fewer rows than work groups take at least, one
+# slab for all tokens, more slabs than the first 64 pairs hold, skipped slots in between.
+@pytest.mark.parametrize("d,f,nslots,T,k", [(128, 2560, 5, 8, 2), (264, 2568, 6, 8, 3), (1032, 4096, 1, 8, 1),
+                                            (64, 4096, 100, 8, 16), (2056, 5000, 3, 8, 2), (8, 8, 2, 3, 2),
+                                            (520, 512, 9, 7, 4)])
+def test_tokens_down_shares(d, f, nslots, T, k):
+    torch = torch_cuda()
+    oracle.set_threads(min(16, os.cpu_count() or 1))
+    say("ffn_tokens shares", d, f, nslots, T, k)
+    rng = np.random.default_rng(d + 7 * f + T)
+    slabs = [synth.expert_slab(1700 + 17 * i + d, d, f, None) for i in range(nslots)]
+    pool = _pool(torch, slabs, d, f)
+    X = rng.standard_normal((T, d)).astype(np.float32)
+    slots = _selection(rng, T, k, nslots)
+    if k > 2:
+        slots[1, 1] = -1
+        slots[T - 1, 0] = nslots
+    w = rng.random((T, k)).astype(np.float32)
+    y = _run(torch, X, pool, nslots, slots, w, d, f)
+    for t, e in enumerate(_expect(X, slabs, slots, w, d, f, nslots)):
+        assert_close(y[t], e, f"shares d={d} f={f} t={t} slots={list(slots[t])}")
+
+
 def test_tokens_invalid_slots_and_single_token():
     """Slots outside [0, n_slots) are skipped (a token with none gets zeros), and one token
     gives what the one-token hit path gives."""
