@@ -321,50 +321,78 @@ __global__ __launch_bounds__(kBlock) void k_combine(const float *a, const float 
 // the selected set (equal to p_S / sum p_S). Lanes r < k write idx[r], w[r] (and the
 // mailbox entries when mbox is set).
 // ---------------------------------------------------------------------------
+//
+// Up to 64 experts, each lane holds one logit and counts those ranked before it, read lane
+// by lane through scalar registers; the lanes then hand theirs to the lane of that rank.
+// (Taking the maximum k times through the LDS crossbar costs six dependent exchanges each:
+// the 64-expert top-8 decode router went from 12.8 to 10.6 us per call with the ranks.)
+// More experts: k rounds of maximum.
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
 __device__ __forceinline__ void select_topk(const double *logit, int n, int k, int lane, int32_t *idx, float *wout,
                                             RouteMailbox *mbox)
 {
-    constexpr int kPer = MOE_MAX_EXPERTS / kWave;
-    double v[kPer];
-    bool taken[kPer];
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        const int e = q * kWave + lane;
-        double l = (e < n) ? logit[e] : -INFINITY;
-        if (l != l) l = -INFINITY;
-        v[q] = l;
-        taken[q] = (e >= n);
-    }
     // Lane r keeps the r-th selected (logit, id).
     double my_l = -INFINITY;
     int my_i = -1;
-    for (int r = 0; r < k; ++r) {
-        double bv = -INFINITY;
-        int bi = 0x7fffffff;
+    if (n <= kWave) {
+        double v = lane < n ? logit[lane] : -INFINITY;
+        if (v != v) v = -INFINITY;
+        int rank = lane < n ? 0 : lane;           // every lane's is another
+        for (int j = 0; j < n; ++j) {
+            const double o = lane_value(v, j);
+            if (lane < n) rank += (o > v || (o == v && j < lane)) ? 1 : 0;
+        }
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const uint32_t lo = __builtin_amdgcn_ds_permute(4 * rank, (int)(uint32_t)u);
+        const uint32_t hi = __builtin_amdgcn_ds_permute(4 * rank, (int)(uint32_t)(u >> 32));
+        my_l = __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+        my_i = __builtin_amdgcn_ds_permute(4 * rank, lane);
+    } else {
+        constexpr int kPer = MOE_MAX_EXPERTS / kWave;
+        double v[kPer];
+        bool taken[kPer];
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
             const int e = q * kWave + lane;
-            if (!taken[q] && (v[q] > bv || (v[q] == bv && e < bi))) {
-                bv = v[q];
-                bi = e;
-            }
+            double l = (e < n) ? logit[e] : -INFINITY;
+            if (l != l) l = -INFINITY;
+            v[q] = l;
+            taken[q] = (e >= n);
         }
+        for (int r = 0; r < k; ++r) {
+            double bv = -INFINITY;
+            int bi = 0x7fffffff;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const double ov = __shfl_xor(bv, o, kWave);
-            const int oi = __shfl_xor(bi, o, kWave);
-            if (ov > bv || (ov == bv && oi < bi)) {
-                bv = ov;
-                bi = oi;
+            for (int q = 0; q < kPer; ++q) {
+                const int e = q * kWave + lane;
+                if (!taken[q] && (v[q] > bv || (v[q] == bv && e < bi))) {
+                    bv = v[q];
+                    bi = e;
+                }
             }
-        }
-        if (lane == r) {
-            my_l = bv;
-            my_i = bi;
-        }
 #pragma unroll
-        for (int q = 0; q < kPer; ++q)
-            if (q * kWave + lane == bi) taken[q] = true;
+            for (int o = 32; o > 0; o >>= 1) {
+                const double ov = __shfl_xor(bv, o, kWave);
+                const int oi = __shfl_xor(bi, o, kWave);
+                if (ov > bv || (ov == bv && oi < bi)) {
+                    bv = ov;
+                    bi = oi;
+                }
+            }
+            if (lane == r) {
+                my_l = bv;
+                my_i = bi;
+            }
+#pragma unroll
+            for (int q = 0; q < kPer; ++q)
+                if (q * kWave + lane == bi) taken[q] = true;
+        }
     }
     const double l0 = __shfl(my_l, 0, kWave);
     const double ex = (lane < k) ? exp(my_l - l0) : 0.0;
@@ -650,7 +678,9 @@ __global__ __launch_bounds__(kBlock) void k_route1(const float *x, const float *
 // at most kRouteBlkItems (expert, segment) items whose segment count divides 8: wave w
 // takes items w, w + 8, ... (at most eight, all loads issued at once), which all lie in
 // segment w mod nseg, so the wave loads that slice of x once. The fp64 partial logits go
-// to LDS and wave 0 sums each expert's segments in order and selects the top-k. One work
+// to LDS and wave 0 sums each expert's segments in order and selects the top-k (widening x
+// once, not per item, and summing a wave's eight items over the lanes together: with the
+// ranked top-k 9.6 -> 8.1 us per Mixtral-shaped call). One work
 // group needs no arrival counter or device-scope fence; the mailbox hand-off is that of
 // k_router.
 // ---------------------------------------------------------------------------
@@ -703,23 +733,31 @@ __global__ __launch_bounds__(kRouteBlkThreads) void k_router_blk(const float *x,
             if (q < nq) xh[q] = xq[m];
         }
     }
+    double xd[4 * kPerLane], acc[kRouteBlkPerWave];   // x is widened once for all items
+#pragma unroll
+    for (int m = 0; m < kPerLane; ++m) {
+        xd[4 * m] = xq[m].x;
+        xd[4 * m + 1] = xq[m].y;
+        xd[4 * m + 2] = xq[m].z;
+        xd[4 * m + 3] = xq[m].w;
+    }
 #pragma unroll
     for (int u = 0; u < kRouteBlkPerWave; ++u) {
         // one item at a time: keeps the scheduler from widening every loaded value to
         // fp64 at once (which would not fit the registers)
         __builtin_amdgcn_sched_barrier(0);
-        double acc = 0.0;
+        acc[u] = 0.0;
 #pragma unroll
         for (int m = 0; m < kPerLane; ++m) {
-            acc += (double)wq[u][m].x * (double)xq[m].x;
-            acc += (double)wq[u][m].y * (double)xq[m].y;
-            acc += (double)wq[u][m].z * (double)xq[m].z;
-            acc += (double)wq[u][m].w * (double)xq[m].w;
+            acc[u] += (double)wq[u][m].x * xd[4 * m];
+            acc[u] += (double)wq[u][m].y * xd[4 * m + 1];
+            acc[u] += (double)wq[u][m].z * xd[4 * m + 2];
+            acc[u] += (double)wq[u][m].w * xd[4 * m + 3];
         }
-        acc = wave_sum(acc);
-        const int item = wv + u * kRouteBlkWaves;
-        if (lane == 0 && item < items) part[item] = acc;
     }
+    const double sum = wave_sums(acc, lane);          // item u's in lanes 8 u ..
+    const int item = wv + (lane >> 3) * kRouteBlkWaves;
+    if ((lane & 7) == 0 && item < items) part[item] = sum;
     __syncthreads();
     for (int e = threadIdx.x; e < n; e += kRouteBlkThreads) {
         double l = 0.0;

@@ -83,3 +83,33 @@ def test_router_empty_batch_is_noop():
     moe.router_topk(x, wr, 2, idx_out=idx, w_out=w)
     torch.cuda.synchronize()
     assert int(idx[0, 0]) == -7
+
+
+# The ranked selection (up to 64 experts, one logit a lane) and the rounds of maximum beyond:
+# the edge between them, every expert selected, ties across the whole row, NaN and infinite
+# logits (NaN ranks as -inf, ids stay valid and distinct).
+@pytest.mark.parametrize("n,k", [(1, 1), (2, 2), (16, 16), (63, 9), (64, 16), (65, 16)])
+def test_router_selection_edges(n, k):
+    torch = torch_cuda()
+    say("router selection", n, k)
+    d, T = 64, 7
+    rng = np.random.default_rng(n * 100 + k)
+    wr = np.zeros((n, d), np.float32)
+    wr[:, 0] = rng.integers(-3, 4, n)              # few distinct logits: many ties
+    X = np.zeros((T, d), np.float32)
+    X[:, 0] = np.arange(1, T + 1)
+    gi, gw = _run(torch, X, wr, k)
+    for t in range(T):
+        l = wr[:, 0].astype(np.float64) * X[t, 0]
+        want = sorted(range(n), key=lambda e: (-l[e], e))[:k]
+        assert list(gi[t]) == want, (t, gi[t], want)
+        p = np.exp(l[want] - l[want[0]])
+        np.testing.assert_allclose(gw[t], p / p.sum(), rtol=3e-7)
+    if n >= 16:
+        wr[3, 0] = np.nan
+        wr[5, 0] = -np.inf
+        gi, gw = _run(torch, X, wr, k)
+        for t in range(T):
+            l = wr[:, 0].astype(np.float64) * X[t, 0]
+            l[np.isnan(l)] = -np.inf
+            assert list(gi[t]) == sorted(range(n), key=lambda e: (-l[e], e))[:k]
