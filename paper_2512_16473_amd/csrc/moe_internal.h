@@ -97,8 +97,9 @@ struct PrefillPlan {
     uint64_t slab_stride;
 };
 size_t prefill_workspace_bytes(int d, int f, int n, int k, int T);
+size_t prefill_workspace_min(int d, int f, int n, int k, int T);   // the least that is taken
 hipError_t launch_prefill(const PrefillPlan &P, const float *X, float *OUT, int32_t *idx,
-                          float *w, void *ws, hipStream_t s);
+                          float *w, void *ws, size_t ws_bytes, hipStream_t s);
 
 int device_cu_count();
 

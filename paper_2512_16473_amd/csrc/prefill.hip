@@ -87,13 +87,17 @@ __device__ __forceinline__ void cast_bf16(const float *x, uint16_t *y, int64_t n
 // tiles that share an expert's token rows (and, side by side, a weight tile) run on one
 // XCD's L2, whatever the number of experts. On an XCD the work groups (one per CU,
 // `slots` of them) take its tiles in rounds; the r tiles of a last, partial round are
-// split over K into s parts each, whose fp32 sums a later kernel adds in order.
+// split over K into s parts each, whose fp32 sums a later kernel adds in order. The sums of
+// up to g.planes parts of a down tile go to as many planes of the output; otherwise each part
+// has a buffer of its own.
 // ---------------------------------------------------------------------------
 struct TilePlan {
     int u0, units;   // first tile of the XCD's run, its length
     int full;        // tiles done whole; the other units - full are split over K
     int s;           // K parts of a split tile
 };
+
+constexpr int kPlanes = 4;   // planes of the down output, at most
 
 __device__ __forceinline__ int tiles_of(int c) { return (c + kTileM - 1) / kTileM; }
 // First row of tile mt of an expert with c tokens (mt == tiles_of(c): c): its ceil(c / 32)
@@ -109,8 +113,9 @@ __device__ __forceinline__ int tile_of_row(int c, int r)
 }
 
 // Plan of XCD xcd for U tiles of nsteps K steps. A split costs about as much as a few K
-// steps (prologue, fp32 sums); s minimises the rounds of parts within the part buffers.
-__device__ __forceinline__ TilePlan tile_plan(int U, int nsteps, int slots, int maxparts, int xcd)
+// steps (prologue, fp32 sums); s minimises the rounds of parts within the planes or the
+// part buffers.
+__device__ __forceinline__ TilePlan tile_plan(int U, int nsteps, int slots, int planes, int maxparts, int xcd)
 {
     TilePlan p;
     p.u0 = (int)((int64_t)U * xcd / kXcds);
@@ -119,7 +124,8 @@ __device__ __forceinline__ TilePlan tile_plan(int U, int nsteps, int slots, int 
     p.full = p.units;
     p.s = 1;
     int best = nsteps;
-    for (int s = 2; r > 0 && s <= kMaxSplit && r * s <= maxparts && s * kMinPartSteps <= nsteps; ++s) {
+    for (int s = 2; r > 0 && s <= kMaxSplit && s * kMinPartSteps <= nsteps; ++s) {
+        if (s > planes && r * s > maxparts) continue;
         const int cost = (r * s + slots - 1) / slots * ((nsteps + s - 1) / s + kSplitSteps);
         if (cost < best) {
             best = cost;
@@ -147,7 +153,7 @@ struct GroupArgs {
     int npairs, n, k;
     int32_t *off, *toff, *tok, *pos;
     TilePlan *plan;                  // [2][8]: gate/up, down
-    int ntiles[2], nsteps[2], maxparts[2], slots;
+    int ntiles[2], nsteps[2], maxparts[2], slots, planes;
     const float *x;
     uint16_t *xb;
     int64_t n8;
@@ -212,7 +218,8 @@ __global__ __launch_bounds__(kGroupThreads) void k_group(GroupArgs g)
     }
     if (t < 2 * kXcds) {
         const int q = t / kXcds;
-        g.plan[t] = tile_plan(total * g.ntiles[q], g.nsteps[q], g.slots, g.maxparts[q], t % kXcds);
+        g.plan[t] = tile_plan(total * g.ntiles[q], g.nsteps[q], g.slots, q ? g.planes : 1, g.maxparts[q],
+                              t % kXcds);
     }
     __syncthreads();
     int e = p0 + lane < p1 ? g.idx[p0 + lane] : 0;
@@ -251,7 +258,9 @@ struct GemmArgs {
     int maxparts, prows;      // part buffers per XCD and their rows
     float *part;              // fp32 sums of the K parts, [8][maxparts][prows][kTileN]
     uint16_t *h;              // gate/up output, bf16 [P][f]
-    float *y;                 // down output, fp32 [P][d]
+    float *y;                 // down output, fp32 [planes][P][d]
+    int planes;
+    size_t plane;             // P d
 };
 
 // Grouped GEMM, 8 waves per work group, one work group per CU, looping over its tiles.
@@ -311,7 +320,7 @@ __device__ __forceinline__ void wait_and_barrier()
 }
 template <bool kGateUp, bool kOnce, int HB>
 __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *lds, int e, int row0, int rows, int nt, int k0,
-                                          int nsteps, int start, float *part)
+                                          int nsteps, int start, float *part, float *y)
 {
     using C = TileCfg<HB>;
     constexpr int NA = C::kAStages, NB = C::kBStages, P = C::kAhead, R = C::kRing, kItems = 2 * HB;
@@ -471,7 +480,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *lds, int e
             }
         } else {
             const int col0 = nt * kTileN + wn * 64 + c4;
-            float *dst = g.y + (size_t)(row0 + tr) * g.d + col0;
+            float *dst = y + (size_t)(row0 + tr) * g.d + col0;
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb)
                 if (col0 + nb * 16 < g.d) *reinterpret_cast<floatx4_t *>(dst + nb * 16) = acc[m][nb];
@@ -497,13 +506,14 @@ __global__ __launch_bounds__(kGemmThreads) void k_moe_gemm(GemmArgs g)
     }
     for (int u = blockIdx.x / kXcds; u < nunits; u += g.slots) {
         int t = u, ks = 0, parts = 1;
-        float *part = nullptr;
+        float *part = nullptr, *y = g.y;
         if (u >= p.full) {
             const int v = u - p.full;
             t = p.full + v / p.s;
             ks = v % p.s;
             parts = p.s;
-            part = g.part + ((size_t)xcd * g.maxparts + v) * g.prows * kTileN;
+            if (!kGateUp && p.s <= g.planes) y += ks * g.plane;
+            else part = g.part + ((size_t)xcd * g.maxparts + v) * g.prows * kTileN;
         }
         t += p.u0;
         int e = -1;   // the last expert whose first tile is at or before t
@@ -521,7 +531,7 @@ __global__ __launch_bounds__(kGemmThreads) void k_moe_gemm(GemmArgs g)
         const int start = m == 1 ? (int)((unsigned)(nt * kStagger) % (unsigned)kn) : 0;
         switch ((rows + 31) >> 5) {
 #define MOE_HB_CASE(N) \
-    case N: gemm_tile<kGateUp, kOnce, N>(g, lds, e, row0, rows, nt, k0, kn, start, part); break;
+    case N: gemm_tile<kGateUp, kOnce, N>(g, lds, e, row0, rows, nt, k0, kn, start, part, y); break;
             MOE_HB_CASE(1) MOE_HB_CASE(2) MOE_HB_CASE(3) MOE_HB_CASE(4)
             MOE_HB_CASE(5) MOE_HB_CASE(6) MOE_HB_CASE(7) MOE_HB_CASE(8)
 #undef MOE_HB_CASE
@@ -594,8 +604,13 @@ __global__ __launch_bounds__(kThreads) void k_prefill_combine(GemmArgs g, const 
         const TilePlan p = g.plan[xcd];
         const int v = u - p.u0 - p.full;
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (v < 0) {
-            s = *reinterpret_cast<const float4 *>(g.y + (size_t)pr * g.d + i);
+        if (v < 0 || p.s <= g.planes) {
+            const float *src = g.y + (size_t)pr * g.d + i;
+            s = *reinterpret_cast<const float4 *>(src);
+            for (int q = 1; v >= 0 && q < p.s; ++q) {
+                const float4 a = *reinterpret_cast<const float4 *>(src + q * g.plane);
+                s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
+            }
         } else {
             const float *src = g.part + (((size_t)xcd * g.maxparts + (size_t)v * p.s) * g.prows + (pr - o0 - tile_row(c, mt))) *
                                             kTileN + i % kTileN;
@@ -624,12 +639,14 @@ struct PrefillWs {
     float *y;
     float *gu_part, *dn_part;   // gate/up part buffers (y is written later), down part buffers
     int gu_parts, dn_parts;     // their number per XCD
+    int planes;                 // of y
 };
 
 // Rows of a part buffer: an expert has at most T tokens.
 int part_rows(int T) { return std::min(T, kTileM); }
 
-size_t layout(int d, int f, int n, int k, int T, uint8_t *base, PrefillWs *ws)
+// The workspace with that many planes of y; its size is returned.
+size_t layout(int d, int f, int n, int k, int T, int nplanes, uint8_t *base, PrefillWs *ws)
 {
     const size_t P = (size_t)T * k;
     size_t o = 0;
@@ -645,12 +662,15 @@ size_t layout(int d, int f, int n, int k, int T, uint8_t *base, PrefillWs *ws)
     uint8_t *tok = take(P * 4);
     uint8_t *pos = take(P * 4);
     uint8_t *h = take(P * f * 2);
-    // fp32 sums: y, and part buffers in what is left of four times its size (plus 48 MiB
-    // from 64 tokens per expert on, where a part buffer has many rows); fewer part buffers
-    // only mean fewer K splits
-    const size_t sums = o;
-    take((size_t)4 * P * d * 4);
-    take((int64_t)T * k < (int64_t)64 * n ? 0 : (size_t)48 << 20);
+    uint8_t *toff = take((size_t)(n + 1) * 4);
+    uint8_t *plan = take(sizeof(TilePlan) * 2 * kXcds);
+    // fp32 sums: the planes of y, which also hold gate/up's part buffers before y is written,
+    // and from 64 tokens per expert on, where a part buffer has many rows, 48 MiB more for the
+    // part buffers of both; fewer part buffers only mean fewer K splits
+    const size_t planes = (size_t)nplanes * P * d * 4;
+    const size_t extra = (int64_t)T * k < (int64_t)64 * n ? 0 : (size_t)48 << 20;
+    uint8_t *y = take(planes);
+    uint8_t *parts = take(extra);
     if (ws) {
         ws->xb = reinterpret_cast<uint16_t *>(xb);
         ws->idx = reinterpret_cast<int32_t *>(idx);
@@ -659,31 +679,43 @@ size_t layout(int d, int f, int n, int k, int T, uint8_t *base, PrefillWs *ws)
         ws->tok = reinterpret_cast<int32_t *>(tok);
         ws->pos = reinterpret_cast<int32_t *>(pos);
         ws->h = reinterpret_cast<uint16_t *>(h);
-        size_t at = sums;
-        ws->toff = reinterpret_cast<int32_t *>(base + at);
-        at += align256((size_t)(n + 1) * 4);
-        ws->plan = reinterpret_cast<TilePlan *>(base + at);
-        at += align256(sizeof(TilePlan) * 2 * kXcds);
+        ws->toff = reinterpret_cast<int32_t *>(toff);
+        ws->plan = reinterpret_cast<TilePlan *>(plan);
         const size_t set = (size_t)kXcds * part_rows(T) * kTileN * 4;   // one buffer on every XCD
-        ws->gu_part = reinterpret_cast<float *>(base + at);
-        ws->gu_parts = (int)std::min<size_t>(kMaxParts, (o - at) / set);
-        ws->y = reinterpret_cast<float *>(base + at);
-        at += align256(P * d * 4);
-        ws->dn_part = reinterpret_cast<float *>(base + at);
-        ws->dn_parts = (int)std::min<size_t>(kMaxParts, (o - at) / set);
+        ws->y = reinterpret_cast<float *>(y);
+        ws->planes = nplanes;
+        ws->gu_part = ws->y;
+        // none below 16 tokens: such a layer is short, its memory holds few part buffers, and
+        // the launch that adds them takes 5 us
+        ws->gu_parts = T < 16 ? 0 : (int)std::min<size_t>(kMaxParts, (planes + extra) / set);
+        ws->dn_part = reinterpret_cast<float *>(parts);
+        ws->dn_parts = (int)std::min<size_t>(kMaxParts, extra / set);
     }
     return o;
 }
 
 }  // namespace
 
-size_t prefill_workspace_bytes(int d, int f, int n, int k, int T) { return layout(d, f, n, k, T, nullptr, nullptr); }
+size_t prefill_workspace_bytes(int d, int f, int n, int k, int T)
+{
+    return layout(d, f, n, k, T, kPlanes, nullptr, nullptr);
+}
+
+// A workspace without room for the tile tables (1.5 KiB at most) beside the planes is taken
+// too; it holds the fewer planes.
+size_t prefill_workspace_min(int d, int f, int n, int k, int T)
+{
+    const size_t tables = align256((size_t)(n + 1) * 4) + align256(sizeof(TilePlan) * 2 * kXcds);
+    return layout(d, f, n, k, T, kPlanes, nullptr, nullptr) - tables;
+}
 
 hipError_t launch_prefill(const PrefillPlan &P, const float *X, float *OUT, int32_t *idx, float *w, void *wsp,
-                          hipStream_t s)
+                          size_t ws_bytes, hipStream_t s)
 {
     PrefillWs ws{};
-    layout(P.d, P.f, P.n, P.k, P.T, static_cast<uint8_t *>(wsp), &ws);
+    int planes = kPlanes;
+    while (planes > 1 && layout(P.d, P.f, P.n, P.k, P.T, planes, nullptr, nullptr) > ws_bytes) --planes;
+    layout(P.d, P.f, P.n, P.k, P.T, planes, static_cast<uint8_t *>(wsp), &ws);
     int32_t *idx_d = idx ? idx : ws.idx;
     float *w_d = w ? w : ws.w;
     hipError_t e;
@@ -707,6 +739,7 @@ hipError_t launch_prefill(const PrefillPlan &P, const float *X, float *OUT, int3
     ga.maxparts[0] = ws.gu_parts;
     ga.maxparts[1] = ws.dn_parts;
     ga.slots = slots;
+    ga.planes = ws.planes;
     ga.x = X;
     ga.xb = ws.xb;
     ga.n8 = (int64_t)P.T * P.d / 8;
@@ -728,6 +761,8 @@ hipError_t launch_prefill(const PrefillPlan &P, const float *X, float *OUT, int3
     g.prows = part_rows(P.T);
     g.h = ws.h;
     g.y = ws.y;
+    g.planes = ws.planes;
+    g.plane = (size_t)P.T * P.k * P.d;
 
     g.a = ws.xb;
     g.plan = ws.plan;
@@ -791,7 +826,7 @@ int moe_prefill_forward(const moe_prefill_desc *P, const float *X_dev, int T, fl
                     moe::aligned16(P->expert_pool),
                 "moe_prefill_forward: device pointers must be 16-byte aligned");
     MOE_REQUIRE(((uintptr_t)workspace & 255u) == 0, "moe_prefill_forward: workspace not 256-byte aligned");
-    const size_t need = moe::prefill_workspace_bytes(P->d, P->f, P->n, P->k, T);
+    const size_t need = moe::prefill_workspace_min(P->d, P->f, P->n, P->k, T);
     MOE_REQUIRE(workspace_bytes >= need, "moe_prefill_forward: workspace %zu < %zu bytes", workspace_bytes, need);
     moe::PrefillPlan plan{};
     plan.d = P->d;
@@ -802,7 +837,8 @@ int moe_prefill_forward(const moe_prefill_desc *P, const float *X_dev, int T, fl
     plan.wr = P->w_router;
     plan.pool = static_cast<const uint8_t *>(P->expert_pool);
     plan.slab_stride = moe_slab_bytes(P->d, P->f);
-    MOE_HIP(moe::launch_prefill(plan, X_dev, OUT_dev, idx_dev, w_dev, workspace, (hipStream_t)stream));
+    MOE_HIP(moe::launch_prefill(plan, X_dev, OUT_dev, idx_dev, w_dev, workspace, workspace_bytes,
+                                (hipStream_t)stream));
     return MOE_OK;
     MOE_GUARD_END
 }

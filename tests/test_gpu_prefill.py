@@ -183,3 +183,49 @@ def test_prefill_tile_edges(d, f, T):
     flip = (near * ulp) @ np.abs(w2).T
     worst = np.max(np.abs(out - ref) - flip, axis=1) / rms
     assert np.all(worst <= 2e-5), (int(np.argmax(worst)), float(worst.max()))
+
+
+# Few tokens on few N tiles: every down tile is split over the output's planes (T = 11: four;
+# the least workspace, without the room for the tile tables: three or fewer), one expert and
+# one token with the smallest planes, and more experts than pairs.
+@pytest.mark.parametrize("d,f,n,k,T", [(1408, 5632, 8, 2, 11), (128, 2048, 1, 1, 1), (256, 1024, 256, 1, 1),
+                                       (384, 4096, 60, 8, 3), (640, 1152, 5, 2, 40)])
+@pytest.mark.parametrize("least", [False, True])
+def test_prefill_planes(d, f, n, k, T, least):
+    torch = torch_cuda()
+    import paper_2512_16473_amd as moe
+    say("prefill planes", d, f, n, k, T, least)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + f + T)
+    stride = moe.slab_bytes(d, f)
+    pool = torch.empty(n * stride // 2, dtype=torch.bfloat16, device="cuda").normal_(0, d ** -0.5, generator=g)
+    wr = torch.empty((n, d), device="cuda").normal_(0, d ** -0.5, generator=g)
+    X = torch.empty((T, d), device="cuda").normal_(0, 1, generator=g)
+    nb = moe.prefill_workspace_bytes(d, f, n, k, T)
+    if least:
+        nb -= ((n + 1) * 4 + 255) // 256 * 256 + 256
+        with pytest.raises(moe.MoeError):
+            moe.prefill_forward(X, wr, pool, d, f, n, k, torch.empty_like(X),
+                                torch.empty(nb - 256, dtype=torch.uint8, device="cuda"))
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    out = torch.full((T, d), float("nan"), device="cuda")
+    idx = torch.zeros((T, k), dtype=torch.int32, device="cuda")
+    w = torch.zeros((T, k), device="cuda")
+    moe.prefill_forward(X, wr, pool, d, f, n, k, out, ws, idx=idx, w=w)
+    torch.cuda.synchronize()
+    ref = torch.zeros((T, d), dtype=torch.float64, device="cuda")
+    xb = X.to(torch.bfloat16).double()
+    scale = torch.zeros((T, 1), dtype=torch.float64, device="cuda")
+    for t in range(T):
+        for r in range(k):
+            W = pool[int(idx[t, r]) * (stride // 2):][:3 * d * f].double()
+            gu, up = W[:f * d].view(f, d) @ xb[t], W[f * d:2 * f * d].view(f, d) @ xb[t]
+            h = (gu / (1 + torch.exp(-gu)) * up).float().to(torch.bfloat16).double()
+            w2 = W[2 * f * d:].view(d, f)
+            ref[t] += w[t, r].double() * (w2 @ h)
+            scale[t] += w[t, r] * h.abs().max() * w2.abs().max()
+    # fp32 sums within 2e-5 RMS; a rounding of h that falls the other way (at most a few of
+    # them) moves an output by one bf16 ulp, 2^-7, of at most the largest h and W2
+    bound = 2e-5 * ref.pow(2).mean(1, keepdim=True).sqrt() + 2 * 2.0 ** -7 * scale
+    assert bool(((out - ref).abs() <= bound).all())
+    assert float((out - ref).norm() / ref.norm()) <= 1e-3
