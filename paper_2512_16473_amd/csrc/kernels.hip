@@ -322,11 +322,14 @@ __global__ __launch_bounds__(kBlock) void k_combine(const float *a, const float 
 // mailbox entries when mbox is set).
 // ---------------------------------------------------------------------------
 //
-// Up to 64 experts, each lane holds one logit and counts those ranked before it, read lane
-// by lane through scalar registers; the lanes then hand theirs to the lane of that rank.
+// With at most 64 experts and 12 per selected one, each lane holds one logit and counts those
+// ranked before it, read lane by lane through scalar registers; the lanes then hand theirs
+// to the lane of that rank. The count takes as long as n, the rounds below as k.
 // (Taking the maximum k times through the LDS crossbar costs six dependent exchanges each:
-// the 64-expert top-8 decode router went from 12.8 to 10.6 us per call with the ranks.)
-// More experts: k rounds of maximum.
+// the 64-expert top-8 decode router went from 12.8 to 10.6 us per call with the ranks; for
+// top-2 of 64 experts (d = 4000) a call takes 16.8 us with ranks and 15.0 with rounds, of 32
+// 10.5 and 10.1.)
+// Otherwise k rounds of maximum.
 __device__ __forceinline__ double lane_value(double v, int lane)
 {
     const uint64_t u = __builtin_bit_cast(uint64_t, v);
@@ -340,7 +343,7 @@ __device__ __forceinline__ void select_topk(const double *logit, int n, int k, i
     // Lane r keeps the r-th selected (logit, id).
     double my_l = -INFINITY;
     int my_i = -1;
-    if (n <= kWave) {
+    if (n <= kWave && n <= 12 * k) {
         double v = lane < n ? logit[lane] : -INFINITY;
         if (v != v) v = -INFINITY;
         int rank = lane < n ? 0 : lane;           // every lane's is another
@@ -942,14 +945,17 @@ hipError_t launch_router(const float *x, const float *wr, int T, int d, int n, i
     if (T != 1) mbox = nullptr, x_host = nullptr, row_src = nullptr;
     if (!row_dst) row_src = nullptr;
     const int cpr = (d / 4 + kWave - 1) / kWave;
-    // Several tokens per work group once one token each would take the chip more than one
-    // round of work groups, or two while the router matrix is small: a lone work group of
-    // four tokens takes longer than one of one (3584 x 64: 24 against 20 us; 4096 x 8: 10
-    // against 8 us for 512 tokens). The tokens' LDS copy holds 64 KiB.
-    const int cus = device_cu_count();
-    if (T > 2 * cus || (T > cus && n > 16)) {
-        if (d <= 4096) return launch_router_batch<4>(x, wr, T, d, n, k, idx, w, s);
-        if (d <= 8192) return launch_router_batch<2>(x, wr, T, d, n, k, idx, w, s);
+    // Several tokens per work group once one token each would take the chip more than two
+    // rounds of work groups, or more than one while the router matrix is large: a lone work
+    // group of four tokens takes longer than one of one (3584 x 64: 24 against 20 us;
+    // 4096 x 8: 10 against 8 us for 512 tokens; 1000 x 64: 10.3 against 9.5 us for 300). Very
+    // small matrices stay with one token each (256 x 4, 4000 tokens: 9.1 against 10.5 us).
+    if (T > 64 && (int64_t)n * d >= 4096) {
+        const int cus = device_cu_count();
+        if (T > 2 * cus || (T > cus && n > 16 && d >= 2048)) {
+            if (d <= 4096) return launch_router_batch<4>(x, wr, T, d, n, k, idx, w, s);
+            if (d <= 8192) return launch_router_batch<2>(x, wr, T, d, n, k, idx, w, s);
+        }
     }
 #define MOE_CPR_CASE(N) \
     if (cpr <= N) return launch_router_cpr<N>(x, wr, T, d, n, k, idx, w, s, mbox, x_host, seq, row_src, row_dst);

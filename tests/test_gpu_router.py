@@ -55,7 +55,8 @@ def test_router_exact_ties():
 # Batches of several tokens per work group: K split over segments (few experts, and more
 # segments than K chunks at d = 64), a K tail, expert groups and token groups that n and T do
 # not fill, the two-token form (d > 4096) and the largest n and k.
-@pytest.mark.parametrize("d,n,k,T", [(64, 5, 5, 1030), (264, 8, 1, 601), (4096, 8, 2, 530), (520, 17, 3, 259),
+@pytest.mark.parametrize("d,n,k,T", [(64, 65, 5, 1030), (520, 8, 1, 601), (4096, 8, 2, 530), (2056, 17, 3, 259),
+                                     (1032, 5, 5, 515),
                                      (3584, 64, 8, 300), (8192, 256, 16, 258), (4104, 30, 2, 513)])
 def test_router_batch_parity(d, n, k, T):
     torch = torch_cuda()
@@ -88,7 +89,8 @@ def test_router_empty_batch_is_noop():
 # The ranked selection (up to 64 experts, one logit a lane) and the rounds of maximum beyond:
 # the edge between them, every expert selected, ties across the whole row, NaN and infinite
 # logits (NaN ranks as -inf, ids stay valid and distinct).
-@pytest.mark.parametrize("n,k", [(1, 1), (2, 2), (16, 16), (63, 9), (64, 16), (65, 16)])
+@pytest.mark.parametrize("n,k", [(1, 1), (2, 2), (16, 16), (12, 1), (13, 1), (63, 9), (64, 5), (64, 6),
+                                 (64, 16), (65, 16)])
 def test_router_selection_edges(n, k):
     torch = torch_cuda()
     say("router selection", n, k)
