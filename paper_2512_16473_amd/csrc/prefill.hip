@@ -81,8 +81,8 @@ __device__ __forceinline__ void cast_bf16(const float *x, uint16_t *y, int64_t n
 // ---------------------------------------------------------------------------
 // Work decomposition of a grouped GEMM, planned on the device from the routing.
 //
-// Expert e's c tokens are cut into m = ceil(c / kTileM) tiles of equal height, rounded up
-// to 16 rows. A GEMM's output tiles, in (expert, N tile, M tile) order with the M tile
+// Expert e's c tokens are cut into m = ceil(c / kTileM) tiles, equal to within a block of
+// 32 rows. A GEMM's output tiles, in (expert, N tile, M tile) order with the M tile
 // fastest, are dealt out to the XCDs in eight contiguous runs of equal length, so that the
 // tiles that share an expert's token rows (and, side by side, a weight tile) run on one
 // XCD's L2, whatever the number of experts. On an XCD the work groups (one per CU,

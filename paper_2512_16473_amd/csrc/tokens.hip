@@ -312,9 +312,9 @@ __global__ __launch_bounds__(kTokThreads) void k_tok_down(TokParams p)
         // token listed a slot twice, and then its pairs go through in groups of T.
         for (int qc = 0; qc < np; qc += p.T) {
             const int nq = min(p.T, np - qc);
-            // rows r, r + 8, ... of the range, two register sets (the next row's segment in
-            // flight while this one is dotted); loads past the last row re-read it. The first
-            // row's are in flight while the segments are staged.
+            // rows r, r + 8, ... of the range, kSets register sets (the next kSets - 1 rows'
+            // segments in flight while this one is dotted); loads past the last row re-read
+            // it. The first rows' are in flight while the segments are staged.
             uint4 a[kSets][CPK];
 #define MOE_TOK_LOAD_ROW(set, rr)                                                                      \
             do {                                                                                       \
