@@ -4,10 +4,10 @@
 // Between one-token decode (one GEMV per hit expert) and prefill (grouped MFMA GEMMs)
 // lies the case of a few tokens per step. Run per token, the GEMV path reads an expert
 // once for every token that selected it; the grouped GEMMs read it once but round the
-// activations to bf16. These kernels keep the GEMV's streaming (each wave reads whole weight rows with 16-byte nontemporal loads) and
-// read each selected slab once: the rows of a slab are dotted with the hidden states of
-// all the tokens that selected it, which sit in LDS (x for gate/up, a segment of h for
-// down). Three kernels on one stream: gate/up/SiLU -> down (split-K over segments of f,
+// activations to bf16. These kernels keep the GEMV's streaming (each wave reads whole
+// weight rows with 16-byte nontemporal loads) and read each selected slab once: the rows of
+// a slab are dotted with the hidden states of all the tokens that selected it, which sit in
+// LDS (x for gate/up, a segment of h for down). Three kernels on one stream: gate/up/SiLU -> down (split-K over segments of f,
 // weighted partials) -> reduce (fixed order). Every block builds the same job table
 // (distinct slots in order of first appearance; each job's (token, rank) pairs in order)
 // from the T*k selections.
