@@ -25,6 +25,7 @@
 
 #include "common.h"
 #include "moe_internal.h"
+#include "tile_plan.h"
 
 namespace moe {
 namespace {
@@ -35,15 +36,11 @@ typedef float floatx4_t __attribute__((ext_vector_type(4)));
 constexpr int kThreads = 256;
 constexpr int kGemmThreads = 512;
 constexpr int kBK = 64;              // K per stage
-constexpr int kXcds = 8;
-constexpr int kTileM = 256;          // tokens per tile, at most
 constexpr int kTileN = 256;          // weight rows per tile
 constexpr int kGuCols = kTileN / 2;  // gate/up: H columns per tile
 constexpr int kLdsBytes = 163840;    // all of a CU's LDS
-constexpr int kMaxSplit = 16;        // K parts per split tile
-constexpr int kMinPartSteps = 4;     // K steps per part, at least
-constexpr int kSplitSteps = 4;       // what a part costs besides its K steps, in K steps
 constexpr int kMaxParts = 64;        // part buffers per XCD
+constexpr int kPlanes = 4;           // planes of the down output, at most
 constexpr int kStagger = 2;          // K steps between the starts of neighbouring N tiles
 
 __device__ __forceinline__ uint16_t f2bf(float f)
@@ -76,64 +73,6 @@ __device__ __forceinline__ void cast_bf16(const float *x, uint16_t *y, int64_t n
         o.w = f2bf(b.z) | ((uint32_t)f2bf(b.w) << 16);
         reinterpret_cast<uint4 *>(y)[i] = o;
     }
-}
-
-// ---------------------------------------------------------------------------
-// Work decomposition of a grouped GEMM, planned on the device from the routing.
-//
-// Expert e's c tokens are cut into m = ceil(c / kTileM) tiles, equal to within a block of
-// 32 rows. A GEMM's output tiles, in (expert, N tile, M tile) order with the M tile
-// fastest, are dealt out to the XCDs in eight contiguous runs of equal length, so that the
-// tiles that share an expert's token rows (and, side by side, a weight tile) run on one
-// XCD's L2, whatever the number of experts. On an XCD the work groups (one per CU,
-// `slots` of them) take its tiles in rounds; the r tiles of a last, partial round are
-// split over K into s parts each, whose fp32 sums a later kernel adds in order. The sums of
-// up to g.planes parts of a down tile go to as many planes of the output; otherwise each part
-// has a buffer of its own.
-// ---------------------------------------------------------------------------
-struct TilePlan {
-    int u0, units;   // first tile of the XCD's run, its length
-    int full;        // tiles done whole; the other units - full are split over K
-    int s;           // K parts of a split tile
-};
-
-constexpr int kPlanes = 4;   // planes of the down output, at most
-
-__device__ __forceinline__ int tiles_of(int c) { return (c + kTileM - 1) / kTileM; }
-// First row of tile mt of an expert with c tokens (mt == tiles_of(c): c): its ceil(c / 32)
-// blocks of 32 rows are spread evenly, so that few padding rows are multiplied.
-__device__ __forceinline__ int tile_row(int c, int mt)
-{
-    return min(c, (int)((uint32_t)((c + 31) >> 5) * (uint32_t)mt / (uint32_t)tiles_of(c)) * 32);
-}
-// the tile that holds row r
-__device__ __forceinline__ int tile_of_row(int c, int r)
-{
-    return (int)(((uint32_t)((r >> 5) + 1) * (uint32_t)tiles_of(c) - 1) / (uint32_t)((c + 31) >> 5));
-}
-
-// Plan of XCD xcd for U tiles of nsteps K steps. A split costs about as much as a few K
-// steps (prologue, fp32 sums); s minimises the rounds of parts within the planes or the
-// part buffers.
-__device__ __forceinline__ TilePlan tile_plan(int U, int nsteps, int slots, int planes, int maxparts, int xcd)
-{
-    TilePlan p;
-    p.u0 = (int)((int64_t)U * xcd / kXcds);
-    p.units = (int)((int64_t)U * (xcd + 1) / kXcds) - p.u0;
-    const int r = p.units % slots;
-    p.full = p.units;
-    p.s = 1;
-    int best = nsteps;
-    for (int s = 2; r > 0 && s <= kMaxSplit && s * kMinPartSteps <= nsteps; ++s) {
-        if (s > planes && r * s > maxparts) continue;
-        const int cost = (r * s + slots - 1) / slots * ((nsteps + s - 1) / s + kSplitSteps);
-        if (cost < best) {
-            best = cost;
-            p.s = s;
-            p.full = p.units - r;
-        }
-    }
-    return p;
 }
 
 // Block 0: the grouping below. Blocks 1 ..: the hidden states rounded to bf16 for the
@@ -600,7 +539,7 @@ __global__ __launch_bounds__(kThreads) void k_prefill_combine(GemmArgs g, const 
         const int o0 = g.off[e], c = g.off[e + 1] - o0;
         const int mt = tile_of_row(c, pr - o0);
         const int u = g.toff[e] * g.ntiles + nt * tiles_of(c) + mt;
-        const int xcd = (int)(((int64_t)kXcds * u + kXcds - 1) / U);   // the run that holds tile u
+        const int xcd = xcd_of_tile(U, u);
         const TilePlan p = g.plan[xcd];
         const int v = u - p.u0 - p.full;
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);

@@ -1,0 +1,82 @@
+// Work decomposition of a grouped GEMM of prefill, planned on the device from the routing
+// (host and device functions: the arithmetic is checked on the CPU).
+//
+// Expert e's c tokens are cut into m = ceil(c / kTileM) tiles, equal to within a block of
+// 32 rows. A GEMM's output tiles, in (expert, N tile, M tile) order with the M tile
+// fastest, are dealt out to the XCDs in eight contiguous runs of equal length, so that the
+// tiles that share an expert's token rows (and, side by side, a weight tile) run on one
+// XCD's L2, whatever the number of experts. On an XCD the work groups (one per CU,
+// `slots` of them) take its tiles in rounds; the r tiles of a last, partial round are
+// split over K into s parts each, whose fp32 sums a later kernel adds in order. The sums of
+// up to `planes` parts of a down tile go to as many planes of the output; otherwise each part
+// has a buffer of its own.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace moe {
+
+constexpr int kXcds = 8;
+constexpr int kTileM = 256;       // tokens per tile, at most
+constexpr int kMaxSplit = 16;     // K parts per split tile
+constexpr int kMinPartSteps = 4;  // K steps per part, at least
+constexpr int kSplitSteps = 4;    // what a part costs besides its K steps, in K steps
+
+struct TilePlan {
+    int u0, units;   // first tile of the XCD's run, its length
+    int full;        // tiles done whole; the other units - full are split over K
+    int s;           // K parts of a split tile
+};
+
+__host__ __device__ inline int tiles_of(int c) { return (c + kTileM - 1) / kTileM; }
+
+// First row of tile mt of an expert with c tokens (mt == tiles_of(c): c). Its ceil(c / 32)
+// blocks of 32 rows are spread evenly, so that few padding rows are multiplied: the first
+// blocks % tiles tiles hold one block more than the others. (No product of blocks and tiles,
+// which passes 32 bits from 5.9 million tokens on.)
+__host__ __device__ inline int tile_row(int c, int mt)
+{
+    const int blocks = (c + 31) >> 5, m = tiles_of(c), q = blocks / m, more = blocks % m;
+    const int row = (mt * q + (mt < more ? mt : more)) * 32;
+    return row < c ? row : c;
+}
+// the tile that holds row r
+__host__ __device__ inline int tile_of_row(int c, int r)
+{
+    const int blocks = (c + 31) >> 5, m = tiles_of(c), q = blocks / m, more = blocks % m;
+    const int b = r >> 5, big = more * (q + 1);   // blocks of the taller tiles
+    return b < big ? b / (q + 1) : more + (b - big) / q;
+}
+
+// Plan of XCD xcd for U tiles of nsteps K steps. A split costs about as much as a few K
+// steps (prologue, fp32 sums); s minimises the rounds of parts within the planes or the
+// part buffers.
+__host__ __device__ inline TilePlan tile_plan(int U, int nsteps, int slots, int planes, int maxparts, int xcd)
+{
+    TilePlan p;
+    p.u0 = (int)((int64_t)U * xcd / kXcds);
+    p.units = (int)((int64_t)U * (xcd + 1) / kXcds) - p.u0;
+    const int r = p.units % slots;
+    p.full = p.units;
+    p.s = 1;
+    int best = nsteps;
+    for (int s = 2; r > 0 && s <= kMaxSplit && s * kMinPartSteps <= nsteps; ++s) {
+        if (s > planes && r * s > maxparts) continue;
+        const int cost = (r * s + slots - 1) / slots * ((nsteps + s - 1) / s + kSplitSteps);
+        if (cost < best) {
+            best = cost;
+            p.s = s;
+            p.full = p.units - r;
+        }
+    }
+    return p;
+}
+
+// The XCD whose run holds tile u of U.
+__host__ __device__ inline int xcd_of_tile(int U, int u)
+{
+    return (int)(((int64_t)kXcds * u + kXcds - 1) / U);
+}
+
+}  // namespace moe

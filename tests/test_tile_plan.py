@@ -1,0 +1,54 @@
+"""The tile arithmetic of the prefill GEMMs (csrc/tile_plan.h), built with g++ and run on
+the host: an expert's token rows are covered once by its tiles whatever their number."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2512_16473_amd", "csrc")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None or not os.path.isdir(os.path.join(ROCM, "include", "hip")):
+        pytest.skip("needs g++ and the HIP headers")
+    so = str(tmp_path_factory.mktemp("tile_plan") / "libtile_plan.so")
+    cmd = [cxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-fsanitize=undefined", "-fsanitize-undefined-trap-on-error",
+           "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"), "-I", CSRC,
+           os.path.join(ROOT, "tests", "native", "tile_plan.cpp"), "-o", so]
+    build = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert build.returncode == 0, build.stderr[-4000:]
+    return ctypes.CDLL(so)
+
+
+def test_tiles_cover_every_row(lib):
+    # every small count, then counts whose blocks times tiles pass 32 bits (the first is
+    # 5,931,521) up to the largest pair count that an int holds with its rounding
+    big = [5931520, 5931521, 6000000, 8388608, 16777215, 16777217, 100000001, 2 ** 31 - 1 - 256]
+    for c in list(range(1, 5000)) + big:
+        assert lib.check_rows(c) == 0, c
+
+
+@pytest.mark.parametrize("slots", [1, 32])
+def test_plans_cover_every_tile(lib, slots):
+    out = (ctypes.c_int * 4)()
+    for U in (1, 7, 8, 9, 31, 255, 256, 257, 1000, 4099):
+        for nsteps in (2, 7, 8, 64, 224):
+            for planes, maxparts in ((1, 0), (1, 64), (4, 0), (4, 23)):
+                at = 0
+                for xcd in range(8):
+                    lib.plan(U, nsteps, slots, planes, maxparts, xcd, out)
+                    u0, units, full, s = out
+                    assert u0 == at and units >= 0 and full <= units
+                    r = units - full
+                    assert (s == 1 and r == 0) or (1 < s <= 16 and 0 < r < slots and full % slots == 0)
+                    assert s <= planes or r * s <= maxparts
+                    assert s == 1 or nsteps // s >= 4
+                    assert all(lib.xcd_of(U, u) == xcd for u in range(u0, u0 + units))
+                    at += units
+                assert at == U
