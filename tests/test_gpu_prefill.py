@@ -229,3 +229,32 @@ def test_prefill_planes(d, f, n, k, T, least):
     bound = 2e-5 * ref.pow(2).mean(1, keepdim=True).sqrt() + 2 * 2.0 ** -7 * scale
     assert bool(((out - ref).abs() <= bound).all())
     assert float((out - ref).norm() / ref.norm()) <= 1e-3
+
+
+# SiLU(g) * u alone: W1 and W3 have one entry a row and W2 is the identity, so g and u are exact
+# products of two bf16 values and the output is the bf16 of SiLU(g) * u itself.
+def test_prefill_swiglu_exact():
+    torch = torch_cuda()
+    say("prefill swiglu")
+    d = f = 128
+    T = 2048
+    rng = np.random.default_rng(11)
+    bf = lambda v: synth.bf16_to_f32(synth.bf16_bits(np.asarray(v, np.float32)))
+    X = np.zeros((T, d), np.float32)
+    X[:, 0] = bf(rng.uniform(0.5, 1.0, T))
+    X[:, 1] = bf(rng.uniform(0.5, 2.0, T) * np.where(np.arange(T) % 8 == 0, 2.0 ** 50, 1.0))
+    X[::16, 0] = 1.0
+    c = bf(rng.uniform(-88, 88, f))
+    c[:8] = bf([-88, -87.5, -80, -60, 88, 1, -1, 0])
+    e = bf(rng.uniform(0.5, 2.0, f) * np.where(np.arange(f) % 4 == 0, 2.0 ** 50, 1.0))
+    W = np.zeros((3, f, d), np.float32)
+    W[0, :, 0], W[1, :, 1], W[2] = c, e, np.eye(d)
+    slab = synth.bf16_bits(W.ravel())
+    out, _, _ = _run(torch, X, np.zeros((1, d), np.float32), _pool_np(torch, [slab], d, f), d, f, 1, 1)
+    g = X[:, :1].astype(np.float64) * c.astype(np.float64)
+    h = g / (1.0 + np.exp(-g)) * (X[:, 1:2].astype(np.float64) * e.astype(np.float64))
+    # Bound: expf within 1 ulp, the sum, the division and the product each rounded once: at most
+    # 2.5 fp32 ulps, 3e-7 relative, before the rounding to bf16.
+    lo, hi = (bf((h * (1 + s * 3e-7)).astype(np.float32)) for s in (-1, 1))
+    off = (out != lo) & (out != hi)
+    assert not off.any(), (int(off.sum()), g[off][:4], h[off][:4], out[off][:4])
