@@ -273,16 +273,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *lds, int e
     const int lr = lane >> 3, lc = ((lane & 7) ^ lr) * 16;
 
     // Token rows: loads past the stage's last repeat it, rows past the tile read its first.
-    // Down's rows are consecutive, so a 32-bit offset from the tile's first reaches them.
-    typename std::conditional<kGateUp, const uint8_t *, uint32_t>::type asrc[C::kALoads];
-    const uint8_t *const abase =
-        reinterpret_cast<const uint8_t *>(g.a + (kGateUp ? 0 : (size_t)row0 * K) + (size_t)k0 * kBK);
+    const uint8_t *asrc[C::kALoads];
+    const uint8_t *const abase = reinterpret_cast<const uint8_t *>(g.a + (size_t)k0 * kBK);
 #pragma unroll
     for (int j = 0; j < C::kALoads; ++j) {
         int r = min(j * 8 + wv, HB * 4 - 1) * kRows + lr;
         r = r < rows ? r : 0;
-        if constexpr (kGateUp) asrc[j] = abase + (size_t)g.tok[row0 + r] * K * 2 + lc;
-        else asrc[j] = (uint32_t)r * (uint32_t)K * 2 + lc;
+        asrc[j] = abase + operand_offset(kGateUp ? g.tok[row0 + r] : row0 + r, K, lc);
     }
     // Weight rows: instruction i of wave wv reads the kRows rows from 64 i + 8 wv; gate/up's
     // second half are the W3 rows, and a down tile with only 128 rows left in W2 (d an odd
@@ -291,17 +288,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, uint8_t *lds, int e
     const uint8_t *const bbase = g.pool + (uint64_t)e * g.slab_stride +
                                  2 * ((kGateUp ? (size_t)0 : (size_t)2 * g.f * g.d) + wrow * K + (size_t)k0 * kBK);
     const size_t bhalf = kGateUp ? (size_t)2 * g.f * K : nt * kTileN + 128 < g.d ? (size_t)256 * K : 0;
-    const uint32_t bquarter = 128u * (uint32_t)K;   // bytes of 64 rows
-    const uint32_t blane = (uint32_t)lr * (uint32_t)K * 2 + lc;
+    const size_t bquarter = operand_offset(64, K, 0);
+    const size_t blane = operand_offset(lr, K, lc);
     auto koff = [&](int stage) {   // steps go round from `start`
         const int ks = stage + start;
         return (size_t)(ks >= nsteps ? ks - nsteps : ks) * kRowBytes;
     };
     auto load_a = [&](int i, int stage, int buf) {
-        const uint8_t *src;
-        if constexpr (kGateUp) src = asrc[i] + koff(stage);
-        else src = abase + koff(stage) + asrc[i];
-        __builtin_amdgcn_global_load_lds((global_cvoid *)src,
+        __builtin_amdgcn_global_load_lds((global_cvoid *)(asrc[i] + koff(stage)),
                                          (lds_void *)(lds + buf * C::kABytes + min(i * 8 + wv, HB * 4 - 1) * 1024), 16, 0,
                                          0);
     };

@@ -79,4 +79,11 @@ __host__ __device__ inline int xcd_of_tile(int U, int u)
     return (int)(((int64_t)kXcds * u + kXcds - 1) / U);
 }
 
+// Byte offset of byte `at` of operand row `row` of K bf16 values. (64 bits: the 256 rows of a
+// down tile span 4 GiB from K = 8.4 million on.)
+__host__ __device__ inline size_t operand_offset(int row, int K, int at)
+{
+    return (size_t)row * (size_t)K * 2 + (size_t)at;
+}
+
 }  // namespace moe

@@ -29,6 +29,8 @@ void plan(int U, int nsteps, int slots, int planes, int maxparts, int xcd, int *
     out[3] = p.s;
 }
 
+size_t offset_of(int row, int K, int at) { return moe::operand_offset(row, K, at); }
+
 int xcd_of(int U, int u) { return moe::xcd_of_tile(U, u); }
 
 }  // extern "C"

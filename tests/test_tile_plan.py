@@ -52,3 +52,12 @@ def test_plans_cover_every_tile(lib, slots):
                     assert all(lib.xcd_of(U, u) == xcd for u in range(u0, u0 + units))
                     at += units
                 assert at == U
+
+
+def test_operand_offsets(lib):
+    # f is bounded by memory alone: one slab of d = 128, f = 8.5 million is 6.5 GB, and the 256
+    # rows of a down tile then span more than 32 bits
+    lib.offset_of.restype = ctypes.c_size_t
+    for K in (128, 14336, 8421376, 8500096, 33554432, 306783488, 2 ** 31 - 128):
+        for row, at in ((0, 0), (7, 112), (64, 0), (252, 96), (255, 112), (2 ** 31 - 1, 112)):
+            assert lib.offset_of(row, K, at) == 2 * row * K + at
