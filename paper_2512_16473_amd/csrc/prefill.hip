@@ -40,7 +40,6 @@ constexpr int kTileN = 256;          // weight rows per tile
 constexpr int kGuCols = kTileN / 2;  // gate/up: H columns per tile
 constexpr int kLdsBytes = 163840;    // all of a CU's LDS
 constexpr int kMaxParts = 64;        // part buffers per XCD
-constexpr int kPlanes = 4;           // planes of the down output, at most
 constexpr int kStagger = 2;          // K steps between the starts of neighbouring N tiles
 
 __device__ __forceinline__ uint16_t f2bf(float f)
@@ -159,7 +158,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_group(GroupArgs g)
     if (t < 2 * kXcds) {
         const int q = t / kXcds;
         g.plan[t] = tile_plan(total * g.ntiles[q], g.nsteps[q], g.slots, q ? g.planes : 1, g.maxparts[q],
-                              t % kXcds);
+                              g.npairs, t % kXcds);
     }
     __syncthreads();
     int e = p0 + lane < p1 ? g.idx[p0 + lane] : 0;
@@ -620,8 +619,11 @@ size_t layout(int d, int f, int n, int k, int T, int nplanes, uint8_t *base, Pre
         ws->planes = nplanes;
         ws->gu_part = ws->y;
         // none below 16 tokens: such a layer is short, its memory holds few part buffers, and
-        // the launch that adds them takes 5 us
-        ws->gu_parts = T < 16 ? 0 : (int)std::min<size_t>(kMaxParts, (planes + extra) / set);
+        // the launch that adds them takes 5 us (which is also why they are not more where y
+        // has more than four planes: 64 tokens on 8 experts of d = 1152, f = 2048 41.8 against
+        // 42.8 us)
+        const size_t gu = (size_t)std::min(nplanes, 4) * P * d * 4 + extra;
+        ws->gu_parts = T < 16 ? 0 : (int)std::min<size_t>(kMaxParts, gu / set);
         ws->dn_part = reinterpret_cast<float *>(parts);
         ws->dn_parts = (int)std::min<size_t>(kMaxParts, extra / set);
     }
@@ -632,22 +634,22 @@ size_t layout(int d, int f, int n, int k, int T, int nplanes, uint8_t *base, Pre
 
 size_t prefill_workspace_bytes(int d, int f, int n, int k, int T)
 {
-    return layout(d, f, n, k, T, kPlanes, nullptr, nullptr);
+    return layout(d, f, n, k, T, max_planes(T), nullptr, nullptr);
 }
 
-// A workspace without room for the tile tables (1.5 KiB at most) beside the planes is taken
-// too; it holds the fewer planes.
+// The least that is taken: four planes without the room for the tile tables (1.5 KiB at
+// most), which then hold fewer.
 size_t prefill_workspace_min(int d, int f, int n, int k, int T)
 {
     const size_t tables = align256((size_t)(n + 1) * 4) + align256(sizeof(TilePlan) * 2 * kXcds);
-    return layout(d, f, n, k, T, kPlanes, nullptr, nullptr) - tables;
+    return layout(d, f, n, k, T, 4, nullptr, nullptr) - tables;
 }
 
 hipError_t launch_prefill(const PrefillPlan &P, const float *X, float *OUT, int32_t *idx, float *w, void *wsp,
                           size_t ws_bytes, hipStream_t s)
 {
     PrefillWs ws{};
-    int planes = kPlanes;
+    int planes = max_planes(P.T);
     while (planes > 1 && layout(P.d, P.f, P.n, P.k, P.T, planes, nullptr, nullptr) > ws_bytes) --planes;
     layout(P.d, P.f, P.n, P.k, P.T, planes, static_cast<uint8_t *>(wsp), &ws);
     int32_t *idx_d = idx ? idx : ws.idx;

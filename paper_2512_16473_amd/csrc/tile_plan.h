@@ -50,9 +50,10 @@ __host__ __device__ inline int tile_of_row(int c, int r)
 }
 
 // Plan of XCD xcd for U tiles of nsteps K steps. A split costs about as much as a few K
-// steps (prologue, fp32 sums); s minimises the rounds of parts within the planes or the
-// part buffers.
-__host__ __device__ inline TilePlan tile_plan(int U, int nsteps, int slots, int planes, int maxparts, int xcd)
+// steps (prologue, fp32 sums), and every plane beyond four one that the combine reads in turn
+// (100 tokens on 8 experts of d = 1152, f = 2048: 42.6 us with four parts, 43.6 with eight);
+// s minimises the rounds of parts within the planes or the part buffers.
+__host__ __device__ inline TilePlan tile_plan(int U, int nsteps, int slots, int planes, int maxparts, int pairs, int xcd)
 {
     TilePlan p;
     p.u0 = (int)((int64_t)U * xcd / kXcds);
@@ -63,7 +64,8 @@ __host__ __device__ inline TilePlan tile_plan(int U, int nsteps, int slots, int 
     int best = nsteps;
     for (int s = 2; r > 0 && s <= kMaxSplit && s * kMinPartSteps <= nsteps; ++s) {
         if (s > planes && r * s > maxparts) continue;
-        const int cost = (r * s + slots - 1) / slots * ((nsteps + s - 1) / s + kSplitSteps);
+        const int reads = s > 4 && s <= planes ? (s - 4) * (1 + pairs / 64) : 0;
+        const int cost = (r * s + slots - 1) / slots * ((nsteps + s - 1) / s + kSplitSteps) + reads;
         if (cost < best) {
             best = cost;
             p.s = s;
@@ -72,6 +74,13 @@ __host__ __device__ inline TilePlan tile_plan(int U, int nsteps, int slots, int 
     }
     return p;
 }
+
+// Planes of the down output, at most, for T tokens. Short prompts have few down tiles and few
+// part buffers or none, so that the planes limit the work groups that read W2: with four, one
+// token on f = 14336, d = 384 ran on 8 of them and took 57.9 us, with eight 43.5 (12 groups of
+// 128-row tiles: 52.8); 63 tokens on 8 experts of f = 14336, d = 256 82.9 -> 70.0. From 128
+// tokens on there are the tiles or the part buffers.
+__host__ __device__ inline int max_planes(int T) { return T < 128 ? 8 : 4; }
 
 // The XCD whose run holds tile u of U.
 __host__ __device__ inline int xcd_of_tile(int U, int u)

@@ -20,14 +20,16 @@ int check_rows(int c)
     return next == c ? 0 : 1 + m;
 }
 
-void plan(int U, int nsteps, int slots, int planes, int maxparts, int xcd, int *out)
+void plan(int U, int nsteps, int slots, int planes, int maxparts, int pairs, int xcd, int *out)
 {
-    const moe::TilePlan p = moe::tile_plan(U, nsteps, slots, planes, maxparts, xcd);
+    const moe::TilePlan p = moe::tile_plan(U, nsteps, slots, planes, maxparts, pairs, xcd);
     out[0] = p.u0;
     out[1] = p.units;
     out[2] = p.full;
     out[3] = p.s;
 }
+
+int planes_of(int T) { return moe::max_planes(T); }
 
 size_t offset_of(int row, int K, int at) { return moe::operand_offset(row, K, at); }
 

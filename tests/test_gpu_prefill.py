@@ -185,8 +185,8 @@ def test_prefill_tile_edges(d, f, T):
     assert np.all(worst <= 2e-5), (int(np.argmax(worst)), float(worst.max()))
 
 
-# Few tokens on few N tiles: every down tile is split over the output's planes (T = 11: four;
-# the least workspace, without the room for the tile tables: three or fewer), one expert and
+# Few tokens on few N tiles: every down tile is split over the output's planes (eight; with the
+# least workspace, four without the room for the tile tables: three or fewer), one expert and
 # one token with the smallest planes, and more experts than pairs.
 @pytest.mark.parametrize("d,f,n,k,T", [(1408, 5632, 8, 2, 11), (128, 2048, 1, 1, 1), (256, 1024, 256, 1, 1),
                                        (384, 4096, 60, 8, 3), (640, 1152, 5, 2, 40)])
@@ -203,7 +203,8 @@ def test_prefill_planes(d, f, n, k, T, least):
     X = torch.empty((T, d), device="cuda").normal_(0, 1, generator=g)
     nb = moe.prefill_workspace_bytes(d, f, n, k, T)
     if least:
-        nb -= ((n + 1) * 4 + 255) // 256 * 256 + 256
+        al = lambda b: (b + 255) // 256 * 256
+        nb = al(T * d * 2) + 4 * al(T * k * 4) + al((n + 1) * 4) + al(T * k * f * 2) + al(4 * T * k * d * 4)
         with pytest.raises(moe.MoeError):
             moe.prefill_forward(X, wr, pool, d, f, n, k, torch.empty_like(X),
                                 torch.empty(nb - 256, dtype=torch.uint8, device="cuda"))

@@ -39,10 +39,10 @@ def test_plans_cover_every_tile(lib, slots):
     out = (ctypes.c_int * 4)()
     for U in (1, 7, 8, 9, 31, 255, 256, 257, 1000, 4099):
         for nsteps in (2, 7, 8, 64, 224):
-            for planes, maxparts in ((1, 0), (1, 64), (4, 0), (4, 23)):
+            for planes, maxparts in ((1, 0), (1, 64), (4, 0), (4, 23), (8, 0)):
                 at = 0
                 for xcd in range(8):
-                    lib.plan(U, nsteps, slots, planes, maxparts, xcd, out)
+                    lib.plan(U, nsteps, slots, planes, maxparts, 100, xcd, out)
                     u0, units, full, s = out
                     assert u0 == at and units >= 0 and full <= units
                     r = units - full
@@ -61,3 +61,15 @@ def test_operand_offsets(lib):
     for K in (128, 14336, 8421376, 8500096, 33554432, 306783488, 2 ** 31 - 128):
         for row, at in ((0, 0), (7, 112), (64, 0), (252, 96), (255, 112), (2 ** 31 - 1, 112)):
             assert lib.offset_of(row, K, at) == 2 * row * K + at
+
+
+@pytest.mark.parametrize("d,f,experts,T", [(128, 14336, 1, 1), (384, 14336, 1, 1), (384, 14336, 1, 127),
+                                           (640, 8192, 2, 1), (1408, 5632, 2, 1), (1408, 5632, 2, 15)])
+def test_short_prompts_fill_the_down_projection(lib, d, f, experts, T):
+    # few tiles: at least as many work groups as four K parts of 128-row tiles would give
+    out = (ctypes.c_int * 4)()
+    groups = 0
+    for xcd in range(8):
+        lib.plan(experts * ((d + 255) // 256), f // 64, 32, lib.planes_of(T), 0, T * experts, xcd, out)
+        groups += out[2] + (out[1] - out[2]) * out[3]
+    assert groups >= 4 * experts * (d // 128)
