@@ -155,10 +155,16 @@ __global__ __launch_bounds__(kGroupThreads) void k_group(GroupArgs g)
             }
         }
     }
-    if (t < 2 * kXcds) {
-        const int q = t / kXcds;
-        g.plan[t] = tile_plan(total * g.ntiles[q], g.nsteps[q], g.slots, q ? g.planes : 1, g.maxparts[q],
-                              g.npairs, t % kXcds);
+    // The plans, by the next four waves: 16 lanes weigh the splits of one (with a thread going
+    // through the splits of a plan the launch took 4.7 us for a token of d = 1408, f = 5632, now 3.2).
+    static_assert(kMaxSplit == 16 && 2 * kXcds * kMaxSplit == MOE_MAX_EXPERTS, "four waves of 16 lanes a plan");
+    if (t >= MOE_MAX_EXPERTS && t < 2 * MOE_MAX_EXPERTS) {
+        const int j = (t - MOE_MAX_EXPERTS) / kMaxSplit, q = j / kXcds, xcd = j % kXcds;
+        const int U = total * g.ntiles[q], r = tile_plan(U, g.slots, xcd, 1).units % g.slots;
+        int key = split_key(r, g.nsteps[q], g.slots, q ? g.planes : 1, g.maxparts[q], g.npairs, t % kMaxSplit + 1);
+#pragma unroll
+        for (int o = 1; o < kMaxSplit; o <<= 1) key = min(key, __shfl_xor(key, o, 64));
+        if (t % kMaxSplit == 0) g.plan[j] = tile_plan(U, g.slots, xcd, key % kMaxSplit + 1);
     }
     __syncthreads();
     int e = p0 + lane < p1 ? g.idx[p0 + lane] : 0;

@@ -49,29 +49,31 @@ __host__ __device__ inline int tile_of_row(int c, int r)
     return b < big ? b / (q + 1) : more + (b - big) / q;
 }
 
-// Plan of XCD xcd for U tiles of nsteps K steps. A split costs about as much as a few K
-// steps (prologue, fp32 sums), and every plane beyond four one that the combine reads in turn
-// (100 tokens on 8 experts of d = 1152, f = 2048: 42.6 us with four parts, 43.6 with eight);
-// s minimises the rounds of parts within the planes or the part buffers.
-__host__ __device__ inline TilePlan tile_plan(int U, int nsteps, int slots, int planes, int maxparts, int pairs, int xcd)
+// What s parts (1 .. kMaxSplit) of each of r split tiles of nsteps K steps cost, and s: the plan
+// takes the s whose key is least. A split costs about as much as a few K steps (prologue,
+// fp32 sums), and every plane beyond four one that the combine reads in turn (100 tokens on 8
+// experts of d = 1152, f = 2048: 42.6 us with four parts, 43.6 with eight); the parts have to
+// fit the planes or the part buffers.
+__host__ __device__ inline int split_key(int r, int nsteps, int slots, int planes, int maxparts, int pairs, int s)
+{
+    constexpr int kNever = 0x7ffffff;
+    int cost = nsteps;
+    if (s > 1) {
+        const int reads = s > 4 && s <= planes ? (s - 4) * (1 + pairs / 64) : 0;
+        cost = (r * s + slots - 1) / slots * ((nsteps + s - 1) / s + kSplitSteps) + reads;
+        if (r == 0 || s * kMinPartSteps > nsteps || (s > planes && r * s > maxparts)) cost = kNever;
+    }
+    return (cost < kNever ? cost : kNever) * kMaxSplit + (s - 1);
+}
+
+// XCD xcd's run of U tiles, with the tiles of a last, partial round in s parts.
+__host__ __device__ inline TilePlan tile_plan(int U, int slots, int xcd, int s)
 {
     TilePlan p;
     p.u0 = (int)((int64_t)U * xcd / kXcds);
     p.units = (int)((int64_t)U * (xcd + 1) / kXcds) - p.u0;
-    const int r = p.units % slots;
-    p.full = p.units;
-    p.s = 1;
-    int best = nsteps;
-    for (int s = 2; r > 0 && s <= kMaxSplit && s * kMinPartSteps <= nsteps; ++s) {
-        if (s > planes && r * s > maxparts) continue;
-        const int reads = s > 4 && s <= planes ? (s - 4) * (1 + pairs / 64) : 0;
-        const int cost = (r * s + slots - 1) / slots * ((nsteps + s - 1) / s + kSplitSteps) + reads;
-        if (cost < best) {
-            best = cost;
-            p.s = s;
-            p.full = p.units - r;
-        }
-    }
+    p.full = s > 1 ? p.units - p.units % slots : p.units;
+    p.s = s;
     return p;
 }
 

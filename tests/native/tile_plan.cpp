@@ -22,7 +22,13 @@ int check_rows(int c)
 
 void plan(int U, int nsteps, int slots, int planes, int maxparts, int pairs, int xcd, int *out)
 {
-    const moe::TilePlan p = moe::tile_plan(U, nsteps, slots, planes, maxparts, pairs, xcd);
+    const int r = moe::tile_plan(U, slots, xcd, 1).units % slots;
+    int key = moe::split_key(r, nsteps, slots, planes, maxparts, pairs, 1);
+    for (int s = 2; s <= moe::kMaxSplit; ++s) {
+        const int k = moe::split_key(r, nsteps, slots, planes, maxparts, pairs, s);
+        if (k < key) key = k;
+    }
+    const moe::TilePlan p = moe::tile_plan(U, slots, xcd, key % moe::kMaxSplit + 1);
     out[0] = p.u0;
     out[1] = p.units;
     out[2] = p.full;
