@@ -423,10 +423,16 @@ size_t moe_prefill_workspace_bytes(const moe_prefill_desc *P, int T);
  * OUT[t] = sum_j w[t][j] FFN_{idx[t][j]}(X[t]) for t < T.
  * X_dev device fp32 [T][d]; OUT_dev device fp32 [T][d]; idx_dev/w_dev device
  * [T][k] routing outputs (nullable). Activations are rounded to bf16 for the
- * matrix cores; accumulation is fp32. The workspace (device, 256-byte aligned,
- * >= moe_prefill_workspace_bytes(P, T)) holds the grouping and the intermediate
- * activations, so the call allocates nothing. d and f must be multiples of 128
- * (d <= MOE_MAX_D); MOE_EINVAL otherwise; T == 0 is a no-op.
+ * matrix cores; accumulation is fp32. The workspace (device, 256-byte aligned) holds the
+ * grouping and the intermediate activations, so the call allocates nothing. It should
+ * have moe_prefill_workspace_bytes(P, T) bytes. A smaller one is taken down to what that
+ * function returned before the tile tables moved into the workspace, with a(b) = b rounded
+ * up to 256:
+ *   a(2 T d) + 4 a(4 T k) + a(4 (n + 1)) + a(2 T k f) + a(16 T k d)
+ *   (+ 48 MiB if T k >= 64 n);
+ * the down projection is then split into fewer parts, so that a short prompt may take
+ * longer and the fp32 sums may round differently. MOE_EINVAL below that. d and f must be
+ * multiples of 128 (d <= MOE_MAX_D); MOE_EINVAL otherwise; T == 0 is a no-op.
  */
 int moe_prefill_forward(const moe_prefill_desc *P, const float *X_dev, int T, float *OUT_dev,
                         int32_t *idx_dev, float *w_dev, void *workspace, size_t workspace_bytes,

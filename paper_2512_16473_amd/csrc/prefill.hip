@@ -567,7 +567,7 @@ __global__ __launch_bounds__(kThreads) void k_prefill_combine(GemmArgs g, const 
     *reinterpret_cast<float4 *>(out + (size_t)t * g.d + i) = acc;
 }
 
-size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+constexpr size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct PrefillWs {
     uint16_t *xb;
@@ -643,12 +643,15 @@ size_t prefill_workspace_bytes(int d, int f, int n, int k, int T)
     return layout(d, f, n, k, T, max_planes(T), nullptr, nullptr);
 }
 
-// The least that is taken: four planes without the room for the tile tables (1.5 KiB at
-// most), which then hold fewer.
+// The least that is taken is what was recommended before the tile tables were kept in the
+// workspace: four planes without the room for the tables, which then hold fewer. One plane and
+// the tables always fit it: three planes are 3 T k d values, at least 3 * 128.
+constexpr size_t table_bytes(int n) { return align256((size_t)(n + 1) * 4) + align256(sizeof(TilePlan) * 2 * kXcds); }
+static_assert(table_bytes(MOE_MAX_EXPERTS) <= (size_t)3 * 128 * 4, "one plane and the tables fit the least workspace");
+
 size_t prefill_workspace_min(int d, int f, int n, int k, int T)
 {
-    const size_t tables = align256((size_t)(n + 1) * 4) + align256(sizeof(TilePlan) * 2 * kXcds);
-    return layout(d, f, n, k, T, 4, nullptr, nullptr) - tables;
+    return layout(d, f, n, k, T, 4, nullptr, nullptr) - table_bytes(n);
 }
 
 hipError_t launch_prefill(const PrefillPlan &P, const float *X, float *OUT, int32_t *idx, float *w, void *wsp,
@@ -657,7 +660,7 @@ hipError_t launch_prefill(const PrefillPlan &P, const float *X, float *OUT, int3
     PrefillWs ws{};
     int planes = max_planes(P.T);
     while (planes > 1 && layout(P.d, P.f, P.n, P.k, P.T, planes, nullptr, nullptr) > ws_bytes) --planes;
-    layout(P.d, P.f, P.n, P.k, P.T, planes, static_cast<uint8_t *>(wsp), &ws);
+    if (layout(P.d, P.f, P.n, P.k, P.T, planes, static_cast<uint8_t *>(wsp), &ws) > ws_bytes) return hipErrorInvalidValue;
     int32_t *idx_d = idx ? idx : ws.idx;
     float *w_d = w ? w : ws.w;
     hipError_t e;

@@ -43,6 +43,22 @@ def test_version_and_sizes():
     assert moe.slab_bytes(0, 8) == 0
 
 
+def test_prefill_workspace_sizes():
+    """The recommended size is at least the least one of the header, and one byte less than
+    that is refused before any HIP call."""
+    lib = moe.lib()
+    al = lambda b: (b + 255) // 256 * 256
+    for d, f, n, k, T in ((128, 128, 256, 1, 1), (128, 128, 1, 1, 1), (384, 640, 60, 8, 3), (4096, 6400, 16, 2, 27),
+                          (256, 512, 4, 2, 127), (256, 512, 4, 2, 128), (4096, 14336, 8, 2, 512), (256, 256, 8, 8, 63),
+                          (256, 256, 8, 8, 64)):
+        least = al(2 * T * d) + 4 * al(4 * T * k) + al(4 * (n + 1)) + al(2 * T * k * f) + al(16 * T * k * d)
+        least += (48 << 20) if T * k >= 64 * n else 0
+        assert moe.prefill_workspace_bytes(d, f, n, k, T) >= least
+        P = _abi.PrefillDesc(d, f, n, k, 256, 256)
+        assert lib.moe_prefill_forward(ctypes.byref(P), 256, T, 256, None, None, 256, least - 1, None) == _abi.MOE_EINVAL
+        assert b"workspace %d < %d bytes" % (least - 1, least) in lib.moe_last_error()
+
+
 def test_argument_errors_do_not_touch_the_device():
     lib = moe.lib()
     # k > n, n too large, d not a multiple of 8: rejected before any HIP call
