@@ -929,7 +929,7 @@ hipError_t launch_router_batch(const float *x, const float *wr, int T, int d, in
     const int groups = (n + kGroupExp - 1) / kGroupExp;
     const int S = groups >= kRouterWaves ? 1 : (kRouterWaves + groups - 1) / groups;
     const size_t lds = (size_t)TB * ((d / 4 + kWave - 1) / kWave) * kWave * sizeof(float4);
-    clear_launch_error();
+    allow_dynamic_lds(k_router_batch<TB>, lds);   // beside up to 8 KiB of static LDS
     hipLaunchKernelGGL(k_router_batch<TB>, dim3((T + TB - 1) / TB), dim3(kRouterBlock), lds, s, x, wr, T, d, n, k, S, idx,
                        w);
     return hipGetLastError();

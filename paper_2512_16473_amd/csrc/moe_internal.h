@@ -103,4 +103,13 @@ hipError_t launch_prefill(const PrefillPlan &P, const float *X, float *OUT, int3
 
 int device_cu_count();
 
+// Allows `lds` bytes of dynamic LDS per work group: more than 64 KiB in all, static LDS
+// included, has to be allowed per kernel (gfx950 has 160 KiB per CU).
+template <typename K>
+void allow_dynamic_lds(K kernel, size_t lds)
+{
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipGetLastError();
+}
+
 }  // namespace moe

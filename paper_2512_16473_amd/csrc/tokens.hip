@@ -393,15 +393,12 @@ int seg_len_tok(int f)
     return (((f + s - 1) / s) + 7) & ~7;
 }
 
-// Allows `lds` bytes of dynamic LDS (beyond 64 KiB it has to be allowed per kernel;
-// gfx950 has 160 KiB per CU) and launches as many work groups as fit on the device at
-// once, at most max_grid.
+// Launches as many work groups with `lds` bytes of dynamic LDS as fit on the device at once, at
+// most max_grid.
 template <typename K>
 hipError_t launch_dyn(K kernel, int64_t max_grid, size_t lds, hipStream_t s, const TokParams &p)
 {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
-    (void)hipGetLastError();
+    allow_dynamic_lds(kernel, lds);
     int occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, kTokThreads, lds) != hipSuccess || occ < 1) {
         (void)hipGetLastError();
