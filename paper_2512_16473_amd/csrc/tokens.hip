@@ -409,6 +409,16 @@ hipError_t launch_dyn(K kernel, int64_t max_grid, size_t lds, hipStream_t s, con
     return hipGetLastError();
 }
 
+// Four register sets where the staging leaves one work group per CU (never below 5 chunks a
+// lane: MOE_MAX_TOKENS rows of fewer stay under kDeepLds), else two.
+template <int CPK>
+hipError_t launch_down(int64_t max_grid, size_t lds, hipStream_t s, const TokParams &p)
+{
+    if constexpr ((size_t)MOE_MAX_TOKENS * CPK * kWave * 32 >= kDeepLds)
+        if (lds >= kDeepLds) return launch_dyn(k_tok_down<CPK, 4>, max_grid, lds, s, p);
+    return launch_dyn(k_tok_down<CPK, 2>, max_grid, lds, s, p);
+}
+
 }  // namespace
 
 size_t tok_workspace_bytes(int T, int k, int d, int f)
@@ -455,13 +465,10 @@ hipError_t launch_tokens(const float *x, const uint8_t *pool, uint64_t stride, i
     const int64_t dn_grid = ((int64_t)max_jobs * p.nseg * d + kDownRows - 1) / kDownRows;
     const int cpk = (p.seg / 8 + kWave - 1) / kWave;
     const size_t lds_h = (size_t)T * cpk * kWave * 32;
-    const bool deep = lds_h >= kDeepLds;
     if (dn_grid > 0) {
         switch (cpk) {
 #define MOE_TOK_CPK(N) \
-    case N: \
-        e = deep ? launch_dyn(k_tok_down<N, 4>, dn_grid, lds_h, s, p) : launch_dyn(k_tok_down<N, 2>, dn_grid, lds_h, s, p); \
-        break;
+    case N: e = launch_down<N>(dn_grid, lds_h, s, p); break;
             MOE_TOK_CPK(1) MOE_TOK_CPK(2) MOE_TOK_CPK(3) MOE_TOK_CPK(4) MOE_TOK_CPK(5) MOE_TOK_CPK(6)
             MOE_TOK_CPK(7) MOE_TOK_CPK(8)
 #undef MOE_TOK_CPK
