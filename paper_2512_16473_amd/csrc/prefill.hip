@@ -75,6 +75,15 @@ __device__ __forceinline__ void cast_bf16(const float *x, uint16_t *y, int64_t n
     }
 }
 
+// Orders the wave's LDS accesses before and after it (the barrier alone orders no memory for
+// the compiler; the hardware runs a wave's LDS accesses in order, so this is no instruction).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Block 0: the grouping below. Blocks 1 ..: the hidden states rounded to bf16 for the
 // matrix cores (independent of the routing, so the two share one launch).
 // Stable counting sort of the pairs p = t*k + r by expert idx[p] (one block): off[e] ..
@@ -183,9 +192,9 @@ __global__ __launch_bounds__(kGroupThreads) void k_group(GroupArgs g)
             g.tok[w] = p / g.k;
             g.pos[p] = w;
         }
-        __builtin_amdgcn_wave_barrier();          // every lane has read before the count moves on
+        wave_sync();                              // every lane has read before the count moves on
         if (live && rank == 0) next[wv][my] += __popcll(same);
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();                              // and reads the new one
     }
 }
 
