@@ -13,6 +13,7 @@ import pytest
 import oracle
 import synth
 from _gpu_util import TOL, rel_err, router_parity, say, torch_cuda
+from _tile_plan import prefill_plans
 
 pytestmark = pytest.mark.gpu
 
@@ -53,13 +54,11 @@ def _pool_np(torch, slabs, d, f):
     return pool.cuda()
 
 
-# (256, 512, 4, 2, 700): 1400 pairs (two chunks of the grouping sort) and ~350 tokens per
-# expert (two 192-token tiles); (384, 640, ...): d not a multiple of 256 (128-row down tiles)
-# and f not a multiple of 256 (two K splits). With one expert per XCD and 32 gate/up work
-# groups resident per XCD, the gate/up tiles of the last partial round are split over K:
-# (512, 1024, 8, 2, 300) 8 tiles per XCD in 4 parts each; (256, 512, 4, 2, 700) two M tiles
-# per expert, 4 parts; (256, 5120, 8, 2, 256) a full round of 32 tiles, then 8 tiles in 4
-# parts; (256, 1024, 16, 2, 520) two experts per XCD, 16 tiles in 2 parts.
+# (256, 512, 4, 2, 700): ~350 tokens per expert (two M tiles) and 128 pairs per wave of the
+# grouping; (384, 640, ...): d not a multiple of 256 (a last down tile of 128 rows). Gate/up
+# tiles are all whole here, K being short; down tiles are split over K: (512, 1024, 8, 2, 300)
+# and (256, 1024, 16, 2, 520) in 4 parts, (384, 640, 16, 4, 130) in 2, (256, 5120, 8, 2, 256)
+# in 16. test_prefill_split_plans covers the other plans.
 @pytest.mark.parametrize("d,f,n,k,T", [(256, 512, 4, 2, 64), (256, 512, 4, 2, 37), (512, 1024, 8, 2, 300),
                                        (384, 640, 16, 4, 130), (256, 256, 8, 1, 1), (256, 512, 64, 8, 48),
                                        (256, 512, 4, 2, 700), (256, 5120, 8, 2, 256), (256, 1024, 16, 2, 520)])
@@ -91,12 +90,13 @@ def test_prefill_full_shape(shape):
     """Configs: one 512-token prompt through a full-size layer with every expert resident,
     in the launch configuration the benchmark times, every token's routing and output
     compared with the oracle.
-    * mixtral (the benchmark's prefill line): one M tile per expert, one expert per XCD,
-      the gate/up tail split in 2 K parts;
-    * phi (d 4096, f 6400, 16 experts top-2): two experts per XCD, 100 gate/up tiles per
-      XCD, the last 4 split in 8 K parts;
-    * fine (d 3584, f 2560, 64 experts top-8, routed experts only): d not a multiple of
-      256 (128-row down tiles) and 64 (token, expert) pairs per expert on average."""
+    * mixtral (the benchmark's prefill line): one M tile per expert, 112 gate/up tiles per
+      XCD, the last 16 in 2 K parts, and all 16 down tiles per XCD in 2;
+    * phi (d 4096, f 6400, 16 experts top-2): 100 gate/up tiles per XCD, the last 4 in 8 K
+      parts, 32 whole down tiles;
+    * fine (d 3584, f 2560, 64 experts top-8, routed experts only): 64 (token, expert) pairs
+      per expert on average, 160 whole gate/up tiles per XCD, 112 down tiles, the last 16 in
+      2 K parts."""
     torch = torch_cuda()
     import paper_2512_16473_amd as moe
     if shape == "mixtral":
@@ -185,11 +185,11 @@ def test_prefill_tile_edges(d, f, T):
     assert np.all(worst <= 2e-5), (int(np.argmax(worst)), float(worst.max()))
 
 
-# Few tokens on few N tiles: every down tile is split over the output's planes (eight; with the
-# least workspace, four without the room for the tile tables: three or fewer), one expert and
-# one token with the smallest planes, and more experts than pairs.
+# Few tokens on few N tiles: every down tile is split over the output's planes (T = 11: five,
+# T = 100: eight; with the least workspace, four without the room for the tile tables: three or
+# fewer), one expert and one token with the smallest planes, and more experts than pairs.
 @pytest.mark.parametrize("d,f,n,k,T", [(1408, 5632, 8, 2, 11), (128, 2048, 1, 1, 1), (256, 1024, 256, 1, 1),
-                                       (384, 4096, 60, 8, 3), (640, 1152, 5, 2, 40)])
+                                       (384, 4096, 60, 8, 3), (640, 1152, 5, 2, 40), (384, 8192, 4, 1, 100)])
 @pytest.mark.parametrize("least", [False, True])
 def test_prefill_planes(d, f, n, k, T, least):
     torch = torch_cuda()
@@ -214,22 +214,64 @@ def test_prefill_planes(d, f, n, k, T, least):
     w = torch.zeros((T, k), device="cuda")
     moe.prefill_forward(X, wr, pool, d, f, n, k, out, ws, idx=idx, w=w)
     torch.cuda.synchronize()
-    ref = torch.zeros((T, d), dtype=torch.float64, device="cuda")
+    _assert_bf16_reference(torch, X, pool, out, idx, w, d, f, n)
+
+
+def _assert_bf16_reference(torch, X, pool, out, idx, w, d, f, n):
+    import paper_2512_16473_amd as moe
+    stride = moe.slab_bytes(d, f)
+    ref = torch.zeros(X.shape, dtype=torch.float64, device="cuda")
     xb = X.to(torch.bfloat16).double()
-    scale = torch.zeros((T, 1), dtype=torch.float64, device="cuda")
-    for t in range(T):
-        for r in range(k):
-            W = pool[int(idx[t, r]) * (stride // 2):][:3 * d * f].double()
-            gu, up = W[:f * d].view(f, d) @ xb[t], W[f * d:2 * f * d].view(f, d) @ xb[t]
-            h = (gu / (1 + torch.exp(-gu)) * up).float().to(torch.bfloat16).double()
-            w2 = W[2 * f * d:].view(d, f)
-            ref[t] += w[t, r].double() * (w2 @ h)
-            scale[t] += w[t, r] * h.abs().max() * w2.abs().max()
+    scale = torch.zeros((X.shape[0], 1), dtype=torch.float64, device="cuda")
+    for e in range(n):
+        t, r = (idx == e).nonzero(as_tuple=True)
+        if t.numel() == 0:
+            continue
+        W = pool[e * (stride // 2):][:3 * d * f].double()
+        gu, up = xb[t] @ W[:f * d].view(f, d).t(), xb[t] @ W[f * d:2 * f * d].view(f, d).t()
+        h = (gu / (1 + torch.exp(-gu)) * up).float().to(torch.bfloat16).double()
+        w2 = W[2 * f * d:].view(d, f)
+        we = w[t, r].double()[:, None]
+        ref.index_add_(0, t, we * (h @ w2.t()))
+        scale.index_add_(0, t, we * h.abs().amax(1, keepdim=True) * w2.abs().max())
     # fp32 sums within 2e-5 RMS; a rounding of h that falls the other way (at most a few of
     # them) moves an output by one bf16 ulp, 2^-7, of at most the largest h and W2
     bound = 2e-5 * ref.pow(2).mean(1, keepdim=True).sqrt() + 2 * 2.0 ** -7 * scale
     assert bool(((out - ref).abs() <= bound).all())
     assert float((out - ref).norm() / ref.norm()) <= 1e-3
+
+
+# Plans with split tiles, each asserted from the routing: gate/up tiles split after whole rounds,
+# with one M tile per expert and with two; down tiles in more parts than there are planes
+# (buffers of their own), several of them, without and after whole rounds, the latter with 17 M
+# tiles per expert. (With as many experts as choices, every expert has all tokens.)
+@pytest.mark.parametrize("d,f,n,k,T,gu,dn", [
+    (1024, 4352, 8, 2, 128, lambda units, full, s: full > 0 and s > 1, lambda units, full, s: True),
+    (1024, 4352, 4, 4, 300, lambda units, full, s: full > 0 and s > 2, lambda units, full, s: units > 1 and s > 4),
+    (384, 6528, 16, 7, 199, lambda units, full, s: s == 1, lambda units, full, s: units > 1 and full == 0 and s > 4),
+    (2048, 1536, 2, 2, 4224, lambda units, full, s: full > 0 and s > 2,
+     lambda units, full, s: full > 0 and units > full + 1 and s > 4)])
+def test_prefill_split_plans(d, f, n, k, T, gu, dn):
+    torch = torch_cuda()
+    import paper_2512_16473_amd as moe
+    say("prefill split plans", d, f, n, k, T)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + f + T)
+    pool = torch.empty(n * moe.slab_bytes(d, f) // 2, dtype=torch.bfloat16, device="cuda")
+    pool.normal_(0, d ** -0.5, generator=g)
+    wr = torch.empty((n, d), device="cuda").normal_(0, d ** -0.5, generator=g)
+    X = torch.empty((T, d), device="cuda").normal_(0, 1, generator=g)
+    ws = torch.empty(moe.prefill_workspace_bytes(d, f, n, k, T), dtype=torch.uint8, device="cuda")
+    out = torch.full((T, d), float("nan"), device="cuda")
+    idx = torch.zeros((T, k), dtype=torch.int32, device="cuda")
+    w = torch.zeros((T, k), device="cuda")
+    moe.prefill_forward(X, wr, pool, d, f, n, k, out, ws, idx=idx, w=w)
+    torch.cuda.synchronize()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    plans = prefill_plans(d, f, n, k, T, torch.bincount(idx.flatten(), minlength=n).tolist(), cus)
+    say("  gate/up", sorted({p[1:] for p in plans[0]}), "down", sorted({p[1:] for p in plans[1]}))
+    assert any(gu(*p[1:]) for p in plans[0]) and any(dn(*p[1:]) for p in plans[1])
+    _assert_bf16_reference(torch, X, pool, out, idx, w, d, f, n)
 
 
 # SiLU(g) * u alone: W1 and W3 have one entry a row and W2 is the identity, so g and u are exact

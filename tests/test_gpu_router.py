@@ -52,10 +52,11 @@ def test_router_exact_ties():
         assert gw[0][0] == gw[0][1] == np.float32(0.5)
 
 
-# Batches of several tokens per work group: K split over segments (few experts, and more
-# segments than K chunks at d = 64), a K tail, expert groups and token groups that n and T do
-# not fill, the two-token form (d > 4096) and the largest n and k.
-@pytest.mark.parametrize("d,n,k,T", [(64, 65, 5, 1030), (520, 8, 1, 601), (4096, 8, 2, 530), (2056, 17, 3, 259),
+# Batches of several tokens per work group: K split over segments (few experts: (520, 8) in four,
+# of three chunks of 256, and (152, 28) in two, of one chunk, so that a segment is empty for
+# every group of experts), rows shorter than a chunk, a K tail, expert groups and token groups
+# that n and T do not fill, the two-token form (d > 4096) and the largest n and k.
+@pytest.mark.parametrize("d,n,k,T", [(64, 65, 5, 1030), (520, 8, 1, 601), (152, 28, 3, 517), (4096, 8, 2, 530), (2056, 17, 3, 259),
                                      (1032, 5, 5, 515),
                                      (3584, 64, 8, 300), (8192, 256, 16, 258), (4104, 30, 2, 513)])
 def test_router_batch_parity(d, n, k, T):

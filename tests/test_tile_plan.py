@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+import _tile_plan as copy
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2512_16473_amd", "csrc")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
@@ -73,3 +75,16 @@ def test_short_prompts_fill_the_down_projection(lib, d, f, experts, T):
         lib.plan(experts * ((d + 255) // 256), f // 64, 32, lib.planes_of(T), 0, T * experts, xcd, out)
         groups += out[2] + (out[1] - out[2]) * out[3]
     assert groups >= 4 * experts * (d // 128)
+
+
+def test_copy_of_the_plan_agrees(lib):
+    """tests/_tile_plan.py, which the GPU tests pick their shapes with."""
+    out = (ctypes.c_int * 4)()
+    assert all(copy.max_planes(T) == lib.planes_of(T) for T in range(1, 600))
+    for U in (0, 1, 8, 31, 97, 256, 272, 1000):
+        for nsteps in (2, 9, 24, 88, 224):
+            for slots, planes, maxparts, pairs in ((32, 1, 0, 5), (32, 1, 64, 900), (32, 4, 24, 900), (32, 8, 0, 5),
+                                                   (32, 8, 48, 250), (31, 4, 64, 64)):
+                for xcd, p in enumerate(copy.plan(U, nsteps, slots, planes, maxparts, pairs)):
+                    lib.plan(U, nsteps, slots, planes, maxparts, pairs, xcd, out)
+                    assert tuple(out) == p, (U, nsteps, slots, planes, maxparts, pairs, xcd)
