@@ -53,7 +53,9 @@ __host__ __device__ inline int tile_of_row(int c, int r)
 // takes the s whose key is least. A split costs about as much as a few K steps (prologue,
 // fp32 sums), and every plane beyond four one that the combine reads in turn (100 tokens on 8
 // experts of d = 1152, f = 2048: 42.6 us with four parts, 43.6 with eight); the parts have to
-// fit the planes or the part buffers.
+// fit the planes or the part buffers. More than four planes are for work groups that would
+// idle, so the parts are one round (4 tokens on 32 experts top-6 of d = 1152, f = 7680: 172 us
+// with two parts, 177 with five in two rounds).
 __host__ __device__ inline int split_key(int r, int nsteps, int slots, int planes, int maxparts, int pairs, int s)
 {
     constexpr int kNever = 0x7ffffff;
@@ -61,7 +63,8 @@ __host__ __device__ inline int split_key(int r, int nsteps, int slots, int plane
     if (s > 1) {
         const int reads = s > 4 && s <= planes ? (s - 4) * (1 + pairs / 64) : 0;
         cost = (r * s + slots - 1) / slots * ((nsteps + s - 1) / s + kSplitSteps) + reads;
-        if (r == 0 || s * kMinPartSteps > nsteps || (s > planes && r * s > maxparts)) cost = kNever;
+        const bool fits = s <= planes ? s <= 4 || r * s <= slots : r * s <= maxparts;
+        if (r == 0 || s * kMinPartSteps > nsteps || !fits) cost = kNever;
     }
     return (cost < kNever ? cost : kNever) * kMaxSplit + (s - 1);
 }

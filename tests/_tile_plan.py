@@ -11,7 +11,8 @@ def max_planes(T):
 def split(r, nsteps, slots, planes, maxparts, pairs):
     best, parts = nsteps, 1
     for s in range(2, MAX_SPLIT + 1):
-        if r == 0 or s * MIN_STEPS > nsteps or (s > planes and r * s > maxparts):
+        fits = s <= 4 or r * s <= slots if s <= planes else r * s <= maxparts
+        if r == 0 or s * MIN_STEPS > nsteps or not fits:
             continue
         reads = (s - 4) * (1 + pairs // 64) if 4 < s <= planes else 0
         cost = -(-r * s // slots) * (-(-nsteps // s) + SPLIT_STEPS) + reads

@@ -49,7 +49,7 @@ def test_plans_cover_every_tile(lib, slots):
                     assert u0 == at and units >= 0 and full <= units
                     r = units - full
                     assert (s == 1 and r == 0) or (1 < s <= 16 and 0 < r < slots and full % slots == 0)
-                    assert s <= planes or r * s <= maxparts
+                    assert s <= min(planes, 4) or r * s <= (slots if s <= planes else maxparts)
                     assert s == 1 or nsteps // s >= 4
                     assert all(lib.xcd_of(U, u) == xcd for u in range(u0, u0 + units))
                     at += units
