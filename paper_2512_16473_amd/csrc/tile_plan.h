@@ -37,16 +37,21 @@ __host__ __device__ inline int tiles_of(int c) { return (c + kTileM - 1) / kTile
 // which passes 32 bits from 5.9 million tokens on.)
 __host__ __device__ inline int tile_row(int c, int mt)
 {
-    const int blocks = (c + 31) >> 5, m = tiles_of(c), q = blocks / m, more = blocks % m;
-    const int row = (mt * q + (mt < more ? mt : more)) * 32;
+    const uint32_t blocks = (uint32_t)(c + 31) >> 5, m = tiles_of(c);
+    if (m <= 1) return mt ? c : 0;
+    const uint32_t q = blocks / m, more = blocks - q * m, t = mt;
+    const int row = (int)(t * q + (t < more ? t : more)) * 32;
     return row < c ? row : c;
 }
 // the tile that holds row r
 __host__ __device__ inline int tile_of_row(int c, int r)
 {
-    const int blocks = (c + 31) >> 5, m = tiles_of(c), q = blocks / m, more = blocks % m;
-    const int b = r >> 5, big = more * (q + 1);   // blocks of the taller tiles
-    return b < big ? b / (q + 1) : more + (b - big) / q;
+    const uint32_t blocks = (uint32_t)(c + 31) >> 5, m = tiles_of(c);
+    if (m <= 1) return 0;
+    const uint32_t q = blocks / m, more = blocks - q * m;
+    const uint32_t b = (uint32_t)r >> 5, tall = more * (q + 1);   // blocks of the taller tiles
+    const bool in = b < tall;
+    return (int)((in ? 0 : more) + (in ? b : b - tall) / (in ? q + 1 : q));
 }
 
 // What s parts (1 .. kMaxSplit) of each of r split tiles of nsteps K steps cost, and s: the plan
