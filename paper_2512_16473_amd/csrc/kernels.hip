@@ -485,10 +485,10 @@ __global__ __launch_bounds__(kRouterBlock) void k_router(const float *X, const f
 // waves). The products are the exact fp64 ones and every expert's are added in the same
 // order, so equal rows give equal logits.
 // The widening (a quarter-rate operation) bounds it: 1500 tokens on 64 experts of d = 3584
-// take 39 us (k_router 71), 4096 tokens on 8 experts of d = 4096 25 us (k_router 41). Eight
-// experts a wave (44 us) or eight tokens a work group (37 and 29 us) need more registers
-// and LDS for little; the fp64 matrix instructions, half the vector units' rate here, took
-// 47 us.
+// take 38 us (k_router 74), 4096 tokens on 8 experts of d = 4096 23 us (k_router 40). Eight
+// experts a wave (44 us, with 39 for this form at the time) or eight tokens a work group (37
+// and 29 us, with 39 and 25) need more registers and LDS for little; the fp64 matrix
+// instructions, half the vector units' rate here, took 47 us.
 // ---------------------------------------------------------------------------
 constexpr int kRouterWaves = kRouterBlock / kWave;
 constexpr int kGroupExp = 4;

@@ -93,7 +93,7 @@ __device__ __forceinline__ void wave_sync()
 // pair's place among its expert's in the 64 is the number of lower lanes with the same
 // expert, found with one ballot per bit of the id. No barrier inside either walk. (Counting
 // earlier pairs in LDS, 1024 pairs per barrier, the launch took 86 us for 10664 pairs and
-// 70 us for 8192; now 16 and 19 us, the cast included.)
+// 70 us for 8192; now 20 and 19 us, the cast included.)
 constexpr int kGroupThreads = 1024;
 constexpr int kGroupWaves = kGroupThreads / 64;
 struct GroupArgs {
@@ -222,8 +222,8 @@ struct GemmArgs {
 // A tile is up to 256 tokens of one expert by 256 weight rows (gate/up: 128 W1 rows and the
 // same 128 W3 rows). Two waves split the tokens and four the weight rows: a wave owns
 // 16 HB tokens and 64 weight rows (gate/up: 32 W1 rows and the matching W3 rows, so an
-// output's gate and up values sit in the same lane), so an operand read from LDS serves
-// 4 to 8 MFMAs. Both operands go from memory to LDS with direct loads (16 bytes per lane,
+// output's gate and up values sit in the same lane), so a token operand read from LDS serves
+// 4 MFMAs and a weight operand HB. Both operands go from memory to LDS with direct loads (16 bytes per lane,
 // the 128 bytes of a K step of 8 rows per instruction), in rings of stages of one K step
 // each; one barrier per step. The token ring is shorter than the weight ring where LDS is
 // short: it is refilled from the L2 and the weights from HBM. In a stage, row r's 16-byte
@@ -235,13 +235,17 @@ struct GemmArgs {
 // columns of one token.
 //
 // Measured (us per layer, before: 192-token tiles, weights through registers, 4 fp32
-// partial planes of the down projection): 512 tokens on 8 Mixtral-shaped experts 605 -> 532,
-// 4096 tokens 4060 -> 2545 (matrix cores busy 53 % of the cycles at the 1.9 GHz the chip
-// holds; without loads in the K loop 1985), 1333 tokens on 64 fine-grained experts 1228 ->
-// 897. At 512 tokens the K loop takes as long with its MFMAs and operand reads removed:
-// the load stream bounds it. Rings of 32-wide stages (deeper, 64-byte row pieces), waves
-// that only load tokens or only weights, and raised wave priority around the MFMAs were
-// no faster.
+// partial planes of the down projection; SiLU the same): 512 tokens on 8 Mixtral-shaped
+// experts 613 -> 538, 4096 tokens 4106 -> 2580 (matrix cores busy 60 % of the cycles, at
+// 1.9 GHz), 1333 tokens on 64 fine-grained experts 1285 -> 832. At 512 tokens the K loop
+// takes as long with its MFMAs and operand reads removed: the load stream bounds it. Rings
+// of 32-wide stages (deeper, 64-byte row pieces), waves that only load tokens or only
+// weights, and raised wave priority around the MFMAs were no faster.
+//
+// A whole down tile sums all of f in one fp32 accumulator per output, where four parts of f
+// were added before. With h exact the sums alone are then 5.0e-7 off (2-norm, against 64 bits)
+// for f = 14336 instead of 2.0e-7, and 1.5e-7 instead of 1.0e-7 for f = 2560; split tiles are
+// as before or closer. The bf16 rounding of x and h puts the outputs 2.9e-3 off either way.
 constexpr int kRowBytes = kBK * 2;
 constexpr int kRows = 1024 / kRowBytes;             // rows per load instruction of a wave
 constexpr int kBBytes = kTileN * kRowBytes;         // weight rows of a stage
@@ -474,7 +478,7 @@ __global__ __launch_bounds__(kGemmThreads) void k_moe_gemm(GemmArgs g)
         const int k0 = nsteps * ks / parts, kn = nsteps * (ks + 1) / parts - k0;
         // An expert's N tiles run side by side. With one M tile each walks its weights from a
         // start of its own, so that they read different columns at a time (neighbours 256
-        // bytes apart: Mixtral-shaped 512-token layer 554 -> 532 us, 7 steps apart 535); with
+        // bytes apart: Mixtral-shaped 512-token layer 570 -> 527 us, 7 steps apart 538); with
         // more, the tiles that share weights or tokens stay in step for the L2.
         const int start = m == 1 ? (int)((unsigned)(nt * kStagger) % (unsigned)kn) : 0;
         switch ((rows + 31) >> 5) {
@@ -724,9 +728,9 @@ hipError_t launch_prefill(const PrefillPlan &P, const float *X, float *OUT, int3
     g.maxparts = ws.gu_parts;
     g.part = ws.gu_part;
     // Below one full M tile per expert on average the weights go by once and are loaded
-    // nontemporally (Mixtral-shaped 512 tokens: 575 -> 532 us, Phi 27 tokens: 415 -> 364 us);
-    // from there on M tiles share them through the caches (4096 tokens: 2545 us, nontemporal
-    // 2670 us; at 256 tokens per expert the two are within 2 %).
+    // nontemporally (Mixtral-shaped 512 tokens: 578 -> 527 us, Phi 27 tokens: 439 -> 390 us);
+    // from there on M tiles share them through the caches (4096 tokens: 2516 us, nontemporal
+    // 2590 us; 1024 tokens, 256 per expert: 928 and 960 us).
     const bool once = (int64_t)P.T * P.k < (int64_t)kTileM * P.n;
     const dim3 grid(kXcds * slots), block(kGemmThreads);
     if (once) hipLaunchKernelGGL((k_moe_gemm<true, true>), grid, block, 0, s, g);

@@ -7,10 +7,10 @@
 // activations to bf16. These kernels keep the GEMV's streaming (each wave reads whole
 // weight rows with 16-byte nontemporal loads) and read each selected slab once: the rows of
 // a slab are dotted with the hidden states of all the tokens that selected it, which sit in
-// LDS (x for gate/up, a segment of h for down). Three kernels on one stream: gate/up/SiLU -> down (split-K over segments of f,
-// weighted partials) -> reduce (fixed order). Every block builds the same job table
-// (distinct slots in order of first appearance; each job's (token, rank) pairs in order)
-// from the T*k selections.
+// LDS (x for gate/up, a segment of h for down). Three kernels on one stream:
+// gate/up/SiLU -> down (split-K over segments of f, weighted partials) -> reduce (fixed
+// order). Every block builds the same job table (distinct slots in order of first
+// appearance; each job's (token, rank) pairs in order) from the T*k selections.
 //
 // Each wave dots one weight row with several tokens, so the arithmetic per byte grows
 // with the tokens per slab. The hidden states are staged as two bf16 parts, hi = bf16(v)
@@ -258,13 +258,13 @@ __global__ __launch_bounds__(kTokThreads) void k_tok_gate_up(TokParams p)
 // (job, segment, row) triples, in that order, are split into one contiguous share of equal
 // weight per resident work group (a row weighs its job's pairs and a constant: jobs with
 // several pairs are bound by the dot products, the others by the weight stream; with
-// rows alone 8 Mixtral-shaped tokens took 421 instead of 405 us). Where a share enters a
+// rows alone 8 Mixtral-shaped tokens took 492 instead of 454 us). Where a share enters a
 // (job, segment), the group stages the h segments of the job's pairs in LDS while its first
 // rows are on their way, and streams its rows of that segment, kSets - 1 of them ahead: four
 // sets where the staging leaves one work group per CU (10 KB in flight per wave with two),
 // two where more groups share the CU. With one work group per 128 rows of a (job, segment),
-// each building the job table and staging before its first load, 8 fine-grained tokens (43
-// slabs) took 446 us, now 379; 8 Phi-shaped ones 250, now 242.
+// each building the job table and staging before its first load, 8 fine-grained tokens took
+// 443 us, now 373; 8 Phi-shaped ones (10 slabs) 260, now 255.
 // CPK = 16-byte chunks per lane of a segment (seg <= CPK * 512).
 template <int CPK, int kSets>
 __global__ __launch_bounds__(kTokThreads) void k_tok_down(TokParams p)
